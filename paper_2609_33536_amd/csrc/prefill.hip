@@ -4,13 +4,9 @@
 // itself).
 //
 // A workgroup of 4 waves serves one (sequence, KV head, tile of query
-// tokens).  Each wave owns 32 query "columns" -- (token, head-in-group)
-// pairs -- and the waves share the K/V blocks, which stream through an LDS
-// ring by direct-to-LDS loads (each wave loads a quarter of every K and V
-// tile; the waves meet at a barrier before a tile is read).
-//
-// Work unit: 32 keys (two TARGET blocks, or one packed BASE pair, or the
-// lone last block).  On 32x32x16 matrix cores:
+// tokens); a wave owns 32 query "columns" -- (token, head-in-group) pairs.
+// The work unit is one pair of blocks, 32 keys (the missing second block of
+// a lone last one is masked).  On 32x32x16 matrix cores, per unit:
 //   S^T (32 keys x 32 columns) = K (32 x 128) . Q^T, 8 products;
 //     lane l holds column l % 32 and keys 8(r/4) + 4(l/32) + r%4, r < 16.
 //   online softmax over those 16 scores (+ the partner lane l ^ 32);
@@ -19,17 +15,19 @@
 //     key steps x 2.  The P operand of key step k is the lane's own scores
 //     r = 8k .. 8k+7, so key index 8(l/32) + i of step k stands for key
 //     16k + 8(i/4) + 4(l/32) + i%4; the V^T operand follows the same order.
-// V^T operands come straight from LDS with transposing reads: 16-bit
-// elements (TARGET) by two ds_read_b64_tr_b16, bytes (BASE) by one
-// ds_read_b64_tr_b8 followed by the byte -> high-byte expansion.  Within
-// each 16-lane group such a read hands lane j element j of the rows the
-// group's lanes point at (row 4a + j/4, element j%4 for 16-bit; row
-// 2a + j/8, byte j%8 for 8-bit), so pointing lane 4a + b at key a, dims
-// d + 4b .. (resp. lane 2a + b at key a, dims d + 8b ..) gives lane j
-// keys a = 0..3 (0..7) of dim d + j.
-//
+// V^T operands come straight from LDS with the transposing read
+// ds_read_b64_tr_b16: within each 16-lane group it hands lane j element j of
+// the rows the group's lanes point at (row 4a + j/4, element j%4), so pointing
+// lane 4a + b at key a, dims d + 4b .. gives lane j keys a = 0..3 of dim d + j.
 // Column c sees keys p < lim(c) = prefix + (its chunk index) + 1.
-// Block-table entries and tags are held in registers per window of 64 blocks.
+//
+// Every unit lies in LDS as 16-bit words whatever its kind, so one branch-free
+// body serves TARGET and BASE blocks and 8-bit pools: TARGET words are loaded
+// straight to their place; bytes (BASE, or 8-bit TARGET) and nibbles (8-bit
+// BASE) are loaded raw and widened in place, once per workgroup (a wave widens
+// the quarter that it loaded).  When every wave fetched and widened the BASE
+// operands for itself, a unit cost a wave 182 vector, 110 scalar and 21 branch
+// instructions; now ~140, ~55 and ~8.
 #include <type_traits>
 
 #include "attn_device.h"
@@ -38,15 +36,12 @@ namespace ekv {
 namespace {
 
 constexpr int kPfWaves = 4;
-constexpr int kPfRing = 4;        // 8 KiB slots
 constexpr int kPfCols = 32;       // query columns per wave
-constexpr int kPfWindow = 64;     // blocks per metadata window: one per lane
+constexpr int kPfWindow = 64;     // pairs per metadata window: one per lane
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short i16x4v __attribute__((ext_vector_type(4)));
-typedef int i32x2v __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) i16x4v* lds_i16x4;
-typedef __attribute__((address_space(3))) i32x2v* lds_i32x2;
 
 template <typename T> struct Mma32;
 template <> struct Mma32<Bf16> {
@@ -78,25 +73,13 @@ __device__ __forceinline__ void split_p<Bf16>(float p0, float p1, uint32_t& hi, 
 }
 template <>
 __device__ __forceinline__ void split_p<Fp16>(float p0, float p1, uint32_t& hi, uint32_t& lo) {
-  float b0, b1, dummy;
-  const uint16_t h0 = Mma<Fp16>::round(p0, &b0), h1 = Mma<Fp16>::round(p1, &b1);
-  const uint16_t e0 = Mma<Fp16>::round(p0 - b0, &dummy), e1 = Mma<Fp16>::round(p1 - b1, &dummy);
-  hi = (uint32_t)h0 | ((uint32_t)h1 << 16);
-  lo = (uint32_t)e0 | ((uint32_t)e1 << 16);
-}
-
-// Prefill's TARGET tile layout: chunk c of token t at position c ^ sw(t),
-// sw(t) = 4 (t & 3) + (t >> 2).  The K reads (16 rows at one chunk per
-// 16 lanes) and the transposing V reads (4 rows x 4 consecutive chunks per
-// 32 lanes) then each touch 16 distinct 16-byte positions of a 256-byte
-// bank cycle, with no bank conflict; the decode layout (c ^ t) puts the
-// V reads' 4 x 2 chunks of a 16-lane group on only 4 positions.
-__device__ __forceinline__ int pf_swizzle(int t) { return 4 * (t & 3) + (t >> 2); }
-
-// Offset in a 4 KiB TARGET tile in HBM of the 16 B that land at LDS chunk p.
-__device__ __forceinline__ uint32_t pf_target_offset(int p) {
-  const int t = p >> 4, pos = p & 15;
-  return t * (2 * kHeadDim) + 16 * (pos ^ pf_swizzle(t));
+  // one packed conversion for the heads (to nearest); p - head is exact, so one
+  // mixed-precision fused multiply-add rounds each remainder into its half
+  typedef _Float16 f16x2v __attribute__((ext_vector_type(2)));
+  const f16x2v h = __builtin_convertvector((f32x2v{p0, p1}), f16x2v);
+  const f16x2v r = {(_Float16)__builtin_fmaf(-1.0f, (float)h[0], p0), (_Float16)__builtin_fmaf(-1.0f, (float)h[1], p1)};
+  hi = __builtin_bit_cast(uint32_t, h);
+  lo = __builtin_bit_cast(uint32_t, r);
 }
 
 // 8 nibbles (element e in byte e/2, low nibble for even e) -> 8 bytes,
@@ -138,387 +121,469 @@ __device__ __forceinline__ void barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Wait until at most 2n of this wave's vector memory instructions are in
-// flight (each ring slot costs a wave two loads); 0 <= n < kPfRing, and a
-// larger n waits as for kPfRing - 1.
-static_assert(kPfRing == 4, "one wait per number of slots that may stay in flight");
-__device__ __forceinline__ void wait_slots(int n) {
-  n = __builtin_amdgcn_readfirstlane(n);
-  if (n >= 3) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-  else if (n == 2) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  else if (n == 1) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+// A unit's slot in LDS: the K rows of both blocks, then the V rows, in groups
+// of 4 rows: 1 KiB (one direct-to-LDS load: 64 lanes x 16 bytes) and 16 bytes
+// of padding.  In a group, 16-byte chunk c of row r sits at position
+// 16 (c / 4) + 4 r + c % 4.  So a K read (16 rows, one chunk) and a transposing
+// V read (4 rows x 4 chunks of one group) touch 16 distinct 16-byte positions
+// of a 256-byte bank cycle, and the head-dim step, the dim tile and the key
+// step of every read are constant offsets from one address per lane.
+constexpr int kGroup = 1024 + 16;
+constexpr int kTilePf = 4 * kGroup;       // 16 rows
+constexpr int kSlotPf = 4 * kTilePf;      // K of both blocks, V of both
+constexpr int kPlanePf = 2 * kTilePf;     // V's offset in a slot
+
+// Offset of row group 2 half of block `member`: quarter q = 2 member + half of
+// a plane, 8 rows, is loaded and widened as one piece.
+__device__ __forceinline__ constexpr uint32_t quarter_offset(int q) { return (q >> 1) * kTilePf + 2 * (q & 1) * kGroup; }
+
+// One direct-to-LDS load: lane l's 16 bytes at base + off go to lds + 16 l.
+// Inline assembly (it writes no register) keeps it out of the compiler's wait
+// insertion, which would wait for every load in flight before each transposing
+// LDS read; the kernels wait with explicit counts.
+__device__ __forceinline__ void dma16(uint64_t base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+               : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// At least two waves per SIMD (at most 256 registers): with one, the matrix
-// cores idle through every softmax.
-// F8: an 8-bit pool (FP8 E5M2 TARGET, 4-bit BASE).  A TARGET pair is
-// loaded into a slot in the byte layout of a packed 16-bit BASE pair (member
-// m from its own block) and a BASE pair's nibbles are staged and widened
-// into that layout, so every unit runs on the byte path with FP16 products.
-template <typename T, int G, bool ELASTIC, bool F8>
-__global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2))) void prefill_kernel(PrefillArgs a) {
-  __shared__ __attribute__((aligned(16))) char ring[kPfRing][kSlotBytes];
-  __shared__ __attribute__((aligned(16))) char nib[F8 ? kPfRing : 1][F8 ? kTileBytes : 16];
-  constexpr int kTileTok = kPfWaves * kPfCols / G;
-  const int s = blockIdx.z;
-  const int kvh = blockIdx.y;
-  const int tile = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int wave = tid >> 6;
-  const int lane = tid & 63;
-  const int n = lane & 31;     // MFMA column
-  const int h = lane >> 5;     // half of the key / head-dim index space
-  // query rows of this sequence, clamped into q and out (never leave them)
-  const int q0 = min(max(a.cu_q[s], 0), a.total_q);
-  const int nq = min(max(a.cu_q[s + 1], q0), a.total_q) - q0;
-  const int t_begin = tile * kTileTok;
-  if (t_begin >= nq) return;   // uniform over the workgroup
-  const int len = max(0, min(a.seq_lens[s], a.max_blocks * kPage));
-  const int prefix = len - nq;
+// Loads and widening of quarters.  A unit costs a quarter kLoads loads (2 of
+// K, 2 of V; half for 8-bit pools) whatever its kind, so that constant counts
+// wait for it: a 16-bit BASE quarter has half the bytes and loads them twice
+// (the copy is overwritten when the quarter is widened), an 8-bit BASE quarter
+// of 512 bytes twice with the two halves of the wave.
+template <bool F8>
+struct Stager {
+  static constexpr int kLoads = F8 ? 2 : 4;
+  static constexpr int kTileP = F8 ? kTileBytes / 2 : kTileBytes;   // a (plane, head) tile in the pool
+  uint32_t src_t, src_b, src_n;   // source offsets in a quarter: words, bytes, nibbles
+  uint32_t raw_n, dst;            // nibbles' place in the raw quarter; this lane's words in the widened one
+  int row;                        // row of the quarter whose 16-element chunk this lane widens
+  uint64_t v_off;                 // K plane -> V plane in the pool
 
-  // this lane's query column and its Q^T operands (dims 16k + 8h .. + 7)
-  const int col = wave * kPfCols + n;
-  const int tq = t_begin + col / G;
-  const int head = col % G;
-  const bool col_ok = tq < nq;
-  const int lim = col_ok ? min(len, prefix + tq + 1) : len;
-  // The softmax uses exp2(s * c - m) with c = |scale| log2(e) >= 0; a
-  // negative scale is applied by negating Q (exact) instead.
-  const float c_scale = fabsf(a.scale_log2);
-  const uint32_t q_sign = a.scale_log2 < 0.f ? 0x80008000u : 0u;
-  u32x4 qop[8];
-  {
-    const uint16_t* qrow =
-        a.q + ((size_t)(q0 + (col_ok ? tq : 0)) * a.num_q_heads + (size_t)kvh * G + head) * kHeadDim;
+  __device__ __forceinline__ Stager(int lane, int num_kv_heads) {
+    src_t = ((lane >> 2) & 3) * 256 + 64 * (lane >> 4) + 16 * (lane & 3);
+    // lane -> (row, chunk) so that 16 consecutive lanes write 16 distinct
+    // positions of a bank cycle when they widen
+    row = (lane >> 1) & 7;
+    const int chunk = 2 * (lane >> 4) + (lane & 1);
+    src_b = row * kHeadDim + 16 * chunk;
+    src_n = 16 * (lane & 31);
+    raw_n = row * (kHeadDim / 2) + 8 * chunk;
+    dst = (row >> 2) * kGroup + 256 * (chunk >> 1) + 64 * (row & 3) + 32 * (chunk & 1);
+    v_off = (uint64_t)num_kv_heads * kTileP;
+  }
+  // Quarter q of a unit, tile: the K tile of the quarter's block (a BASE
+  // pair's: the packed tile), slot: the unit's slot (LDS address).
+  __device__ __forceinline__ void load(uint64_t tile, bool base, int q, uint32_t slot) const {
+    const uint32_t to = slot + quarter_offset(q);
+    const uint64_t packed = tile + (uint32_t)(q >> 1) * (kTileP / 2);
+    if constexpr (F8) {
+      const uint32_t off = base ? src_n : src_b;
+      const uint64_t src = base ? packed + (q & 1) * 8 * (kHeadDim / 2) : tile + (q & 1) * 8 * kHeadDim;
+      dma16(src, off, to);
+      dma16(src + v_off, off, to + kPlanePf);
+    } else {
+      const uint32_t off = base ? src_b : src_t;
+      const uint64_t src = base ? packed + (q & 1) * 8 * kHeadDim : tile + (q & 1) * 8 * 2 * kHeadDim;
+      const uint64_t src2 = src + (base ? 0 : 1024);
+      dma16(src, off, to);
+      dma16(src2, off, to + kGroup);
+      dma16(src + v_off, off, to + kPlanePf);
+      dma16(src2 + v_off, off, to + kPlanePf + kGroup);
+    }
+  }
+  // After quarter q has landed: bytes or nibbles -> words in place (every
+  // lane's reads precede the wave's writes), and zero V rows for keys at or
+  // past `valid` (their slots may hold anything, and 0 * NaN would poison
+  // the products).  key0: the unit's first key.
+  __device__ __forceinline__ void widen(char* slot, bool base, int q, int key0, int valid, int lane) const {
+    char* at = slot + quarter_offset(q);
+    if (F8 || base) {
+      u32x4 raw[2];
+#pragma unroll
+      for (int pl = 0; pl < 2; ++pl) {
+        if (F8 && base) {
+          const u32x2 x = *reinterpret_cast<const u32x2*>(at + pl * kPlanePf + raw_n);
+          const u32x2 lo = widen_nibbles(x.x), hi = widen_nibbles(x.y);
+          raw[pl] = u32x4{lo.x, lo.y, hi.x, hi.y};
+        } else {
+          raw[pl] = *reinterpret_cast<const u32x4*>(at + pl * kPlanePf + 16 * lane);
+        }
+      }
+#pragma unroll
+      for (int pl = 0; pl < 2; ++pl) {
+        *reinterpret_cast<u32x4*>(at + pl * kPlanePf + dst) = expand_base8(raw[pl].xy);
+        *reinterpret_cast<u32x4*>(at + pl * kPlanePf + dst + 16) = expand_base8(raw[pl].zw);
+      }
+    }
+    if (key0 + 2 * kPage > valid && key0 + 8 * q + row >= valid) {
+      *reinterpret_cast<u32x4*>(at + kPlanePf + dst) = u32x4{0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4*>(at + kPlanePf + dst + 16) = u32x4{0u, 0u, 0u, 0u};
+    }
+  }
+};
+
+// The block table of one sequence in windows of 64 pairs: lane l holds the K
+// tile addresses of both blocks of pair w0 + l, and a mask the pairs' modes, so
+// that a unit's loads read their addresses from a lane, with no LDS or memory
+// round trip.  The next window's entries are fetched a window ahead.
+template <bool ELASTIC, bool F8>
+struct PairTable {
+  const int32_t* row;
+  const uint8_t* tags;
+  int base_lo = 0, base_hi = 0;   // BASE pairs by boundaries (when the tags are not used)
+  bool use_tags = false;
+  int nblk, units, num_blocks;
+  uint64_t pool, block_bytes;
+  int w0 = 0;
+  uint64_t addr0 = 0, addr1 = 0, base_mask = 0;   // the current window
+  int next0 = 0, next1 = 0;                       // the next one, as read
+  bool next_base = false;
+
+  __device__ __forceinline__ PairTable(const PrefillArgs& a, int s, int kvh, int nblk_, int lane) : nblk(nblk_) {
+    row = a.bt + (size_t)s * a.max_blocks;
+    tags = a.tags ? a.tags + (size_t)s * a.max_blocks : nullptr;
+    units = (nblk + 1) >> 1;
+    num_blocks = a.num_blocks;
+    block_bytes = (uint64_t)2 * a.num_kv_heads * Stager<F8>::kTileP;
+    pool = reinterpret_cast<uint64_t>(a.pool) + (uint64_t)kvh * Stager<F8>::kTileP;
+    if constexpr (ELASTIC) {
+      int b0 = -1, b1 = -1;
+      if (a.bounds) {
+        b0 = a.bounds[2 * s];
+        b1 = a.bounds[2 * s + 1];
+      }
+      if (b0 >= 0) {
+        base_lo = b0;
+        base_hi = b1;
+      } else if (tags) {
+        use_tags = true;
+      }
+    }
+    fetch(0, lane);
+    enter();
+    if (units > kPfWindow) fetch(kPfWindow, lane);
+  }
+  __device__ __forceinline__ void fetch(int from, int lane) {
+    const int p = from + lane;
+    next0 = next1 = 0;
+    next_base = false;
+    if (p < units) {
+      next0 = row[2 * p];
+      next1 = 2 * p + 1 < nblk ? row[2 * p + 1] : next0;   // a lone last block stands in for the missing one (masked)
+      if constexpr (ELASTIC) next_base = use_tags ? tags[2 * p] != 0 : (p >= base_lo && p < base_hi);
+    }
+  }
+  __device__ __forceinline__ void enter() {
+    const int b0 = (unsigned)next0 < (unsigned)num_blocks ? next0 : 0;   // never leave the pool
+    const int b1 = (unsigned)next1 < (unsigned)num_blocks ? next1 : 0;
+    addr0 = pool + (uint64_t)(uint32_t)b0 * block_bytes;
+    addr1 = next_base ? addr0 : pool + (uint64_t)(uint32_t)b1 * block_bytes;   // (a BASE pair lies in its first block)
+    base_mask = __builtin_amdgcn_ballot_w64(next_base);
+  }
+  // unit u (nondecreasing over calls); its mode
+  __device__ __forceinline__ bool seek(int u, int lane) {
+    if (u >= w0 + kPfWindow) {
+      w0 = u & ~(kPfWindow - 1);
+      enter();
+      if (w0 + kPfWindow < units) fetch(w0 + kPfWindow, lane);
+    }
+    return ELASTIC && ((base_mask >> (u & (kPfWindow - 1))) & 1) != 0;
+  }
+  __device__ __forceinline__ uint64_t tile(int u, int member) const {
+    const uint64_t a = member ? addr1 : addr0;
+    const int l = u & (kPfWindow - 1);
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(a >> 32), l) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((uint32_t)a, l);
+  }
+};
+
+// One wave's 32 query columns of a (sequence, KV head).
+template <typename T, int G>
+struct Columns {
+  u32x4 q[8];              // Q^T operands: dims 16 k + 8 h .. + 7
+  size_t row;              // this lane's query row (element offset in q and out)
+  int lim, lim_all;        // keys this lane's column sees; keys every column sees
+  bool ok;
+  float c_scale;           // |scale| log2(e): a negative scale negates the queries instead (exact)
+  f32x16 o[4];
+  float m = -__builtin_inff(), l = 0.f;   // reference max (log2 units, the same in lanes l and l ^ 32), this lane's sum
+
+  // first column col0 of the sequence's chunk; q0, nq: its rows; prefix, len: its keys
+  __device__ __forceinline__ Columns(const PrefillArgs& a, int kvh, int q0, int nq, int len, int col0, int lane) {
+    const int col = col0 + (lane & 31), h = lane >> 5;
+    const int tq = col / G, head = col % G, prefix = len - nq;
+    ok = tq < nq;
+    lim = ok ? min(len, prefix + tq + 1) : len;
+    lim_all = min(len, prefix + col0 / G + 1);
+    c_scale = fabsf(a.scale_log2);
+    const uint32_t sign = a.scale_log2 < 0.f ? 0x80008000u : 0u;
+    row = ((size_t)(q0 + (ok ? tq : 0)) * a.num_q_heads + (size_t)kvh * G + head) * kHeadDim;
 #pragma unroll
     for (int k = 0; k < 8; ++k)
-      qop[k] = col_ok ? (*reinterpret_cast<const u32x4*>(qrow + 16 * k + 8 * h) ^ q_sign) : u32x4{0u, 0u, 0u, 0u};
-  }
-  // keys every column of this wave sees (below that no mask is needed)
-  const int lim_wave = min(len, prefix + t_begin + wave * kPfCols / G + 1);
-  const int t_last = min(nq, t_begin + kTileTok) - 1;
-  const int kv_end = max(1, min(len, prefix + t_last + 1));
-  const int nblk = (kv_end + kPage - 1) / kPage;
-
-  // mode of the sequence
-  int base_lo = 0, base_hi = 0;
-  bool use_tags = false;
-  if constexpr (ELASTIC) {
-    int b0 = -1, b1 = -1;
-    if (a.bounds) {
-      b0 = a.bounds[2 * s];
-      b1 = a.bounds[2 * s + 1];
-    }
-    if (b0 >= 0) {
-      base_lo = 2 * b0;
-      base_hi = 2 * b1;
-    } else if (a.tags) {
-      use_tags = true;
-    }
-  }
-
-  // each wave loads quarter `wave` of every K and V tile of a slot, at this
-  // LDS address (plus the slot's offset); TARGET tiles in prefill's own
-  // swizzle, BASE tiles as in decode
-  const DmaOffsets dma = dma_offsets(lane + 64 * wave);
-  const uint32_t dma_tgt = pf_target_offset(lane + 64 * wave);
-  const uint32_t lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr)&ring[0][0] + 1024 * wave);
-  // a (plane, head) tile in HBM: 4 KiB of 16-bit words, or 2 KiB of bytes
-  constexpr int kTileP = F8 ? kTileBytes / 2 : kTileBytes;
-  const size_t block_bytes = (size_t)2 * a.num_kv_heads * kTileP;
-  const char* pool = reinterpret_cast<const char*>(a.pool) + (size_t)kvh * kTileP;
-  const size_t v_off = (size_t)a.num_kv_heads * kTileP;
-  // F8: offset of this lane's 16 B inside its member's tile (waves 0, 1 load
-  // member 0, waves 2, 3 member 1), and this wave's share of the staging area
-  const uint32_t dma_member = dma.base[0] - (uint32_t)(wave >> 1) * (kTileBytes / 2);
-  const uint32_t nib_wave = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr)&nib[0][0] + 512 * wave);
-  const int32_t* btrow = a.bt + (size_t)s * a.max_blocks;
-  const uint8_t* tagrow = a.tags ? a.tags + (size_t)s * a.max_blocks : nullptr;
-
-  // LDS reads.  K (A operand of S^T): key row m = lane % 32.  V^T: the
-  // 16-lane group g16 covers dims 16 (g16 & 1) .. + 15 of each 32-dim tile;
-  // within it, position i16 supplies the row address of the transposing read.
-  const int t_row = n & 15;
-  const int g16 = lane >> 4;
-  const int i16 = lane & 15;
-  const int tr_a = i16 >> 2, tr_b = i16 & 3;   // 16-bit: key a, dims + 4b
-  const int b8_a = i16 >> 1, b8_b = i16 & 1;   // 8-bit: key a, dims + 8b
-  // byte offsets inside a slot.  The swizzles only flip the address bits
-  // that select the step, so each per-step offset is a per-lane base XOR a
-  // constant: K rows kt ^ 32k (16-bit) and kb ^ 16k (bytes) for the 16-dim
-  // step k; V^T rows vt[half] ^ 64t (16-bit, per half of the key step) and
-  // vb ^ 32t (bytes) for the 32-dim tile t.
-  const int f_row = pf_swizzle(t_row);
-  const uint32_t off_kt = t_row * (2 * kHeadDim) + 16 * (h ^ (f_row & 1)) + 32 * (f_row >> 1);
-  const uint32_t off_kb = (n >> 4) * (kTileBytes / 2) + t_row * kHeadDim + 16 * tau(t_row) + 8 * h;
-  uint32_t off_vt[2];
+      q[k] = ok ? (*reinterpret_cast<const u32x4*>(a.q + row + 16 * k + 8 * h) ^ sign) : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int key = 8 * half + 4 * h + tr_a;
-    const int x = 2 * (g16 & 1) + (tr_b >> 1);
-    const int f = pf_swizzle(key);
-    off_vt[half] = kTileBytes + key * (2 * kHeadDim) + 16 * (x ^ (f & 3)) + 64 * (f >> 2) + 8 * (tr_b & 1);
+    for (int t = 0; t < 4; ++t) o[t] = f32x16{};
   }
-  const int keyb = 8 * (b8_a >> 2) + 4 * h + (b8_a & 3);
-  const uint32_t off_vb =
-      kTileBytes + keyb * kHeadDim + 16 * ((g16 & 1) ^ (tau(keyb) & 1)) + 32 * (tau(keyb) >> 1) + 8 * b8_b;
-
-  f32x16 o[4];
+  __device__ __forceinline__ f32x16 scores(const u32x4 (&k)[8]) const {
+    f32x16 s = f32x16{};
 #pragma unroll
-  for (int t = 0; t < 4; ++t) o[t] = f32x16{};
-  float m_run = -__builtin_inff();   // reference max, log2 units (same in lanes l and l ^ 32)
-  float l_run = 0.f;                 // running sum over this lane's keys
-
-  for (int w0 = 0; w0 < nblk; w0 += kPfWindow) {
-    const int w1 = min(nblk, w0 + kPfWindow);
-    barrier();   // the ring is free: every wave is done with the last window's units
-    // The window's metadata stays in registers: lane i holds the table entry
-    // of block w0 + i, and a 64-bit mask holds the BASE tags, so a DMA issue
-    // reads its block id with one lane read and no LDS round trip.
-    int bt_lane = 0;
-    bool base_lane = false;
-    if (w0 + lane < w1) {
-      const int bt = btrow[w0 + lane];
-      bt_lane = (unsigned)bt < (unsigned)a.num_blocks ? bt : 0;   // never leave the pool
-      if constexpr (ELASTIC)
-        base_lane = use_tags ? tagrow[w0 + lane] != 0 : (w0 + lane >= base_lo && w0 + lane < base_hi);
+    for (int i = 0; i < 8; ++i) s = Mma32<T>::mma(k[i], q[i], s);
+    return s;
+  }
+  // Scores enter the softmax as s * c in log2 units (c is returned).  Units
+  // that every column sees whole fold c into the max and the exponent; the
+  // others scale first and then set masked keys to -inf, so that a zero
+  // scale never multiplies an infinity (0 * -inf is NaN).
+  __device__ __forceinline__ float mask(f32x16& s, int key0, int h) const {
+    if (key0 + 2 * kPage <= lim_all) return c_scale;
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      s[r] = key0 + 8 * (r >> 2) + 4 * h + (r & 3) >= lim ? -__builtin_inff() : s[r] * c_scale;
+    return 1.0f;
+  }
+  // Moves the reference max if some column's unit max exceeds it by more than
+  // 2^8 (wave-uniform result); then *shift = old - new reference (log2).
+  __device__ __forceinline__ bool advance(const f32x16& s, float c, float* shift) {
+    const float m0 = max3(s[0], s[1], s[2]), m1 = max3(s[3], s[4], s[5]);
+    const float m2 = max3(s[6], s[7], s[8]), m3 = max3(s[9], s[10], s[11]);
+    const float m4 = max3(s[12], s[13], s[14]);
+    float mx = max3(max3(m0, m1, m2), max3(m3, m4, s[15]), m0);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = __builtin_fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c;
+    const bool moved = __builtin_amdgcn_ballot_w64(mx > m + 8.0f) != 0;
+    const float to = moved ? __builtin_fmaxf(m, mx) : m;
+    *shift = m - to;
+    m = to;
+    return moved;
+  }
+  // P = exp2(s c - ref) as 16-bit heads and remainders; returns the lane's sum.
+  __device__ __forceinline__ float probabilities(const f32x16& s, float c, float ref, u32x4 (&hi)[2], u32x4 (&lo)[2]) const {
+    float sum[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      float p[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) p[i] = fast_exp2(__builtin_fmaf(s[8 * ks + i], c, -ref));
+      sum[ks] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      uint32_t wh[4], wl[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) split_p<T>(p[2 * i], p[2 * i + 1], wh[i], wl[i]);
+      hi[ks] = u32x4{wh[0], wh[1], wh[2], wh[3]};
+      lo[ks] = u32x4{wl[0], wl[1], wl[2], wl[3]};
     }
-    const uint64_t base_mask = __builtin_amdgcn_ballot_w64(base_lane);   // bit i: block w0 + i is BASE
+    return sum[0] + sum[1];
+  }
+  __device__ __forceinline__ void accumulate(const u32x4 (&v)[4], u32x4 p) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) o[t] = Mma32<T>::mma(v[t], p, o[t]);
+  }
+  __device__ __forceinline__ void rescale(float f) {
+    l *= f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) scale_in_place(o[t], f);
+  }
+  __device__ __forceinline__ float total() const {   // the column's sum
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+    return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+};
 
-    auto is_base = [&](int blk) -> bool {
-      if constexpr (!ELASTIC) return false;
-      else return ((base_mask >> (blk - w0)) & 1) != 0;
-    };
-    int ib = w0, issued = 0, consumed = 0;
-    auto issue = [&]() {
-      const bool base = is_base(ib);
-      const char* src = pool + (size_t)(uint32_t)__builtin_amdgcn_readlane(bt_lane, ib - w0) * block_bytes;
-      const uint32_t dst = lds_wave + (uint32_t)(issued & (kPfRing - 1)) * kSlotBytes;
-      if constexpr (F8) {
-        if (base) {
-          // both members' nibbles (2 KiB per plane) to the staging area: this
-          // wave moves 512 B of K and of V with half its lanes
-          const uint32_t nd = nib_wave + (uint32_t)(issued & (kPfRing - 1)) * kTileBytes;
-          if (lane < 32) {
-            const char* ns = src + 512 * wave + 16 * lane;
-            __builtin_amdgcn_global_load_lds(static_cast<const void*>(ns), (lds_ptr)(size_t)nd, 16, 0, 0);
-            __builtin_amdgcn_global_load_lds(static_cast<const void*>(ns + v_off), (lds_ptr)(size_t)(nd + kTileBytes / 2),
-                                             16, 0, 0);
-          }
-          ib += 2;
-        } else {
-          // member m of a TARGET pair from its own block; a lone last block
-          // stands in for the missing member 1 (whose keys are masked)
-          const bool pair = ib + 1 < w1;
-          const int b1 = pair ? __builtin_amdgcn_readlane(bt_lane, ib + 1 - w0) : 0;
-          const char* srcm = (wave >> 1) && pair ? pool + (size_t)(uint32_t)b1 * block_bytes : src;
-          __builtin_amdgcn_global_load_lds(static_cast<const void*>(srcm + dma_member), (lds_ptr)(size_t)dst, 16, 0, 0);
-          __builtin_amdgcn_global_load_lds(static_cast<const void*>(srcm + v_off + dma_member),
-                                           (lds_ptr)(size_t)(dst + kTileBytes), 16, 0, 0);
-          ib += pair ? 2 : 1;
-        }
-      } else {
-        const uint32_t off = base ? dma.base[0] : dma_tgt;
-        __builtin_amdgcn_global_load_lds(static_cast<const void*>(src + off), (lds_ptr)(size_t)dst, 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(static_cast<const void*>(src + v_off + off),
-                                         (lds_ptr)(size_t)(dst + kTileBytes), 16, 0, 0);
-        ib += base ? 2 : 1;
+// Dim tile t of a column's output: this lane holds dims 32 t + 8 u + 4 h .. + 3.
+template <typename T>
+__device__ __forceinline__ void store_tile(const PrefillArgs& a, size_t row, const f32x16& o, float inv, int t, int h) {
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const size_t idx = row + 32 * t + 8 * u + 4 * h;
+    store_pair<T>(a.out, idx, o[4 * u] * inv, o[4 * u + 1] * inv, a.out_fp32);
+    store_pair<T>(a.out, idx + 2, o[4 * u + 2] * inv, o[4 * u + 3] * inv, a.out_fp32);
+  }
+}
+
+// Per-lane offsets of the K and V^T reads in a slot.
+__device__ __forceinline__ uint32_t k_read_offset(int lane) {
+  const int n = lane & 31;   // key row; chunk 2 k + h of step k
+  return (n >> 4) * kTilePf + ((n >> 2) & 3) * kGroup + 64 * (n & 3) + 16 * (lane >> 5);
+}
+__device__ __forceinline__ uint32_t v_read_offset(int lane) {
+  const int i = lane & 15, key = i >> 2, d = i & 3;
+  return kPlanePf + (lane >> 5) * kGroup + 64 * key + 16 * (2 * ((lane >> 4) & 1) + (d >> 1)) + 8 * (d & 1);
+}
+__device__ __forceinline__ void read_k(const char* at, u32x4 (&k)[8]) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) k[i] = *reinterpret_cast<const u32x4*>(at + 256 * (i >> 1) + 32 * (i & 1));
+}
+__device__ __forceinline__ void read_v(const char* at, u32x4 (&v)[2][4]) {
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const char* p = at + ks * kTilePf + 256 * t;
+      const u32x2 a = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)p));
+      const u32x2 b = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(p + 2 * kGroup)));
+      v[ks][t] = u32x4{a.x, a.y, b.x, b.y};
+    }
+}
+
+// A sequence's rows and keys, clamped into q, out and the table.
+struct Extent {
+  int q0, nq, len;
+  __device__ __forceinline__ Extent(const PrefillArgs& a, int s) {
+    q0 = min(max(a.cu_q[s], 0), a.total_q);
+    nq = min(max(a.cu_q[s + 1], q0), a.total_q) - q0;
+    len = max(0, min(a.seq_lens[s], a.max_blocks * kPage));
+  }
+  // keys that chunk row t sees, at least 1
+  __device__ __forceinline__ int seen(int t) const { return max(1, min(len, len - nq + t + 1)); }
+};
+
+// ---- 4 waves x 32 columns over shared units --------------------------------
+// Software pipeline, one barrier a unit: the body of unit i runs the softmax of
+// unit i while the matrix cores run the P.V products of unit i - 1 and the
+// scores of unit i + 1 (both in the same basic block, so the compiler
+// interleaves them), reads K of unit i + 1 and V of unit i, widens unit i + 2
+// and issues the loads of unit i + 3.  4 slots, 66,560 B of LDS: two
+// workgroups, two waves per SIMD (232 registers).
+// Measured in one run against the kernel before (32-key units fetched and
+// widened per wave, no pipeline), append of the chunk included: 8B chunked
+// prefill (16 x (2048 prefix, half BASE, + 512), 32 / 8 heads, bf16) 537 ->
+// 481 us; 8-bit pool, 2 x (8192 + 1024), 64 / 8 heads 958 -> 852 us; 3 short
+// fp16 prompts 36 -> 28 us.
+// What bounds it: matrix work under the power limit.  The kernel runs 1.5x the
+// algorithmic flops (P's remainder); with random operands a plain 8192^3 bf16
+// product reaches 1.2-1.3 PFLOP/s on this card (1.7 with zeros), which is
+// ~370 us for this work, and leaving out the exponentials or the LDS reads
+// changes the time by only 2-4 %.  Not kept: 64 columns per wave with one wave
+// per SIMD (half the LDS reads, but a lone wave issues a vector instruction
+// only every ~4.9 cycles: 4-6 % slower); the remainders p - head by
+// v_dot2_f32_bf16 (fewer instructions, but they occupy the matrix pipe: 5 % slower).
+constexpr int kPfRing = 4;
+
+template <typename T, int G, bool ELASTIC, bool F8>
+__global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_kernel(PrefillArgs a) {
+  __shared__ __attribute__((aligned(16))) char ring[kPfRing * kSlotPf];
+  constexpr int kTileTok = kPfWaves * kPfCols / G;
+  const int tiles = (a.max_q_len + kTileTok - 1) / kTileTok;
+  // Workgroup -> (sequence, KV head), query tile; the last tiles (most keys)
+  // first.  Ids go round robin over the 8 XCDs: with a multiple of 8 KV heads
+  // all tiles of one (sequence, KV head) go to one XCD and share its L2, and
+  // every XCD gets a KV head of every sequence; otherwise whole (sequence, KV
+  // head)s would load the XCDs unevenly (12 of them: 1.4x the time), and the
+  // tiles are spread instead.
+  const int groups = a.batch * a.num_kv_heads;
+  int grp, tile;
+  if (a.num_kv_heads % 8 == 0) {
+    const int i = blockIdx.x >> 3;
+    grp = 8 * (i / tiles) + (blockIdx.x & 7);
+    tile = tiles - 1 - i % tiles;
+  } else {
+    grp = blockIdx.x % groups;
+    tile = tiles - 1 - blockIdx.x / groups;
+  }
+  const int s = grp / a.num_kv_heads, kvh = grp % a.num_kv_heads;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const Extent x(a, s);
+  const int t_begin = tile * kTileTok;
+  if (t_begin >= x.nq) return;   // uniform over the workgroup
+
+  Columns<T, G> col(a, kvh, x.q0, x.nq, x.len, t_begin * G + wave * kPfCols, lane);
+  const int nblk = (x.seen(min(x.nq, t_begin + kTileTok) - 1) + kPage - 1) / kPage;
+  PairTable<ELASTIC, F8> table(a, s, kvh, nblk, lane);
+  const int units = table.units;
+  // the units this wave's own columns see (none if it has no column)
+  const int t_wave = t_begin + wave * kPfCols / G;
+  const int own_units = t_wave >= x.nq ? 0 : (x.seen(min(x.nq, t_wave + (kPfCols + G - 1) / G) - 1) + 31) >> 5;
+  const int valid = min(x.len, nblk * kPage);   // V rows of keys at or past this are zeroed
+  const Stager<F8> stager(lane, a.num_kv_heads);
+  const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr)&ring[0]);
+  const char* k_at = ring + k_read_offset(lane);
+  const char* v_at = ring + v_read_offset(lane);
+  auto slot_of = [](int u) -> uint32_t { return (uint32_t)(u & (kPfRing - 1)) * kSlotPf; };
+
+  int issued = 0;
+  uint32_t modes = 0;       // bit 0: the unit issued last is BASE
+  auto issue = [&]() {      // (past the last unit, its loads again, into a slot that nothing reads)
+    const int u = min(issued, units - 1);
+    const bool base = table.seek(u, lane);
+    stager.load(table.tile(u, wave >> 1), base, wave, lds + slot_of(issued));
+    modes = (modes << 1) | (base ? 1u : 0u);
+    ++issued;
+  };
+  // this wave's quarter of unit u, when IN_FLIGHT units after it may still be loading
+  auto stage = [&](int u, auto in_flight) {
+    wait_loads<Stager<F8>::kLoads * decltype(in_flight)::value>();
+    stager.widen(ring + slot_of(u), ELASTIC && ((modes >> (issued - 1 - u)) & 1u) != 0u, wave, 32 * u, valid, lane);
+  };
+
+  u32x4 hi[2], lo[2], k[8], v[2][4];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    hi[ks] = lo[ks] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[ks][t] = u32x4{0u, 0u, 0u, 0u};
+  }
+  auto products = [&]() {   // O += V^T P^T of the unit whose P and V are in registers
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      col.accumulate(v[ks], hi[ks]);
+      col.accumulate(v[ks], lo[ks]);
+    }
+  };
+#pragma unroll 1
+  for (int u = 0; u < kPfRing - 1; ++u) issue();
+  stage(0, std::integral_constant<int, kPfRing - 2>{});
+  stage(1, std::integral_constant<int, kPfRing - 3>{});
+  barrier();
+  read_k(k_at, k);
+  f32x16 sc = col.scores(k);
+
+#pragma unroll 1
+  for (int i = 0; i < units; ++i) {
+    barrier();   // units i and i + 1 are whole; unit i - 1's slot is free
+    issue();
+    if (i < own_units) {
+      const float c = col.mask(sc, 32 * i, h);
+      float shift;
+      const bool moved = col.advance(sc, c, &shift);
+      read_k(k_at + slot_of(i + 1), k);
+      products();
+      read_v(v_at + slot_of(i), v);
+      const f32x16 next = col.scores(k);
+      u32x4 nhi[2], nlo[2];
+      float sum = col.probabilities(sc, c, col.m, nhi, nlo);
+      // (kept in this block, beside the products: not sunk below the rescale's branch)
+      asm volatile("" : "+v"(nhi[0]), "+v"(nhi[1]), "+v"(nlo[0]), "+v"(nlo[1]), "+v"(sum));
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        hi[ks] = nhi[ks];
+        lo[ks] = nlo[ks];
       }
-      ++issued;
-    };
-#pragma unroll
-    for (int k = 0; k < kPfRing - 1; ++k)
-      if (ib < w1) issue();
-
-    for (int cb = w0; cb < w1;) {
-      // the unit: a BASE pair (one slot), two TARGET blocks, or a lone block
-      const bool base = is_base(cb);
-      const bool two = !F8 && !base && cb + 1 < w1;   // 8-bit units take one slot each
-      const int nslots = two ? 2 : 1;
-      while (issued < consumed + nslots) issue();   // (the ring normally runs ahead)
-      wait_slots(issued - consumed - nslots);
-      barrier();   // every wave's quarters have landed; the slots of the last unit are free
-      while (ib < w1 && issued - consumed < kPfRing) issue();
-
-      const char* sa = ring[consumed & (kPfRing - 1)];
-      const char* sbk = ring[(consumed + (two ? 1 : 0)) & (kPfRing - 1)];
-      const int key0 = cb * kPage;
-      const bool full = base || cb + 1 < w1;   // two blocks in the unit (else the lone last one)
-      const int nkeys = full ? 32 : 16;
-      if constexpr (F8) {
-        if (base) {
-          // widen the staged nibbles: each lane makes one 16-byte chunk of K
-          // and one of V (member m, row t, chunk q at position q ^ tau(t))
-          const int p = lane + 64 * wave;
-          const int m = p >> 7, t = (p >> 3) & 15, qc = p & 7;
-          const char* ns = nib[consumed & (kPfRing - 1)] + m * (kTileBytes / 4) + t * (kHeadDim / 2) + 8 * qc;
-          char* bd = ring[consumed & (kPfRing - 1)] + m * (kTileBytes / 2) + t * kHeadDim + 16 * (qc ^ tau(t));
-#pragma unroll
-          for (int plane = 0; plane < 2; ++plane) {
-            const u32x2 x = *reinterpret_cast<const u32x2*>(ns + plane * (kTileBytes / 2));
-            const u32x2 lo = widen_nibbles(x.x), hi = widen_nibbles(x.y);
-            *reinterpret_cast<u32x4*>(bd + plane * kTileBytes) = u32x4{lo.x, lo.y, hi.x, hi.y};
-          }
-          barrier();   // the widened tiles are visible to every wave
-        }
-      }
-
-      // The block kind only changes how the K and V operands are fetched:
-      // each fetch phase branches once on it (not once per step), so a
-      // phase's LDS reads are all in flight together, while the products
-      // and the accumulators stay in code common to both kinds.
-      auto unit = [&](auto masked) {
-        constexpr bool kMasked = decltype(masked)::value;
-        // ---- S^T = K Q^T ----
-        u32x4 kop[8];
-        if (F8 || (ELASTIC && base)) {
-#pragma unroll
-          for (int k = 0; k < 8; ++k)
-            kop[k] = expand_base8(*reinterpret_cast<const u32x2*>(sa + (off_kb ^ (16 * k))));
-        } else {
-          const char* sk = n < 16 ? sa : sbk;   // the lane's key row is in its member's slot
-#pragma unroll
-          for (int k = 0; k < 8; ++k) kop[k] = *reinterpret_cast<const u32x4*>(sk + (off_kt ^ (32 * k)));
-        }
-        f32x16 sc = f32x16{};
-#pragma unroll
-        for (int k = 0; k < 8; ++k) sc = Mma32<T>::mma(kop[k], qop[k], sc);
-
-        // V^T operands of key step ks (16 keys); step 0 is fetched before the
-        // softmax, so its LDS reads overlap the wait for the S^T products
-        struct VOps {
-          u32x4 t[4];
-        };
-        auto fetch_v = [&](int ks) -> VOps {
-          VOps r;
-          if (F8 || (ELASTIC && base)) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              const i32x2v raw =
-                  __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2)(sa + ks * (kTileBytes / 2) + (off_vb ^ (32 * t))));
-              r.t[t] = expand_base8(u32x2{(uint32_t)raw[0], (uint32_t)raw[1]});
-              if (F8 && kMasked) {   // 8-bit TARGET keys at or past the sequence end: zero V
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                  const int key = 16 * ks + 8 * (e >> 2) + 4 * h + (e & 3);
-                  if (key0 + key >= len) r.t[t][e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
-                }
-              }
-            }
-          } else {
-            const char* sl = ks == 0 ? sa : sbk;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              uint32_t w[4];
-#pragma unroll
-              for (int half = 0; half < 2; ++half) {
-                const u32x2 pr = __builtin_bit_cast(
-                    u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(sl + (off_vt[half] ^ (64 * t)))));
-                w[2 * half] = pr.x;
-                w[2 * half + 1] = pr.y;
-              }
-              if (kMasked) {   // keys at or past the sequence end: zero V (their slots hold anything)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                  const int key = 16 * ks + 8 * (e >> 2) + 4 * h + (e & 3);
-                  if (key0 + key >= len) w[e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
-                }
-              }
-              r.t[t] = u32x4{w[0], w[1], w[2], w[3]};
-            }
-          }
-          return r;
-        };
-        const VOps v0 = fetch_v(0);
-
-        // ---- online softmax over this lane's 16 keys (+ lane ^ 32) ----
-        // Scores enter the softmax as s * c in log2 units.  Interior units fold
-        // c into the max and the exponent; masked units scale first and then
-        // set masked keys to -inf, so that a zero scale never multiplies an
-        // infinity (0 * -inf is NaN).
-        const float c = kMasked ? 1.0f : c_scale;
-        if constexpr (kMasked) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = 8 * (r >> 2) + 4 * h + (r & 3);
-            sc[r] = (key >= nkeys || key0 + key >= lim) ? -__builtin_inff() : sc[r] * c_scale;
-          }
-        }
-        const float m0 = max3(sc[0], sc[1], sc[2]), m1 = max3(sc[3], sc[4], sc[5]);
-        const float m2 = max3(sc[6], sc[7], sc[8]), m3 = max3(sc[9], sc[10], sc[11]);
-        const float m4 = max3(sc[12], sc[13], sc[14]);
-        float mx = max3(max3(m0, m1, m2), max3(m3, m4, sc[15]), m0);
-        {
-          const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-          mx = max3(__uint_as_float(sw[0]), __uint_as_float(sw[1]), __uint_as_float(sw[1])) * c;
-        }
-        if (__builtin_amdgcn_ballot_w64(mx > m_run + 8.0f)) {
-          const float m_new = fmaxf(m_run, mx);
-          const float alpha = fast_exp2(m_run - m_new);
-          l_run *= alpha;
-#pragma unroll
-          for (int t = 0; t < 4; ++t) scale_in_place(o[t], alpha);
-          m_run = m_new;
-        }
-        // P = exp2(s c - m); its 16-bit head by truncation, the remainder
-        // p - head rounded to 16 bits
-        u32x4 phi[2], plo[2];
-        float lsum[2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          float p[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) p[i] = fast_exp2(__builtin_fmaf(sc[8 * ks + i], c, -m_run));
-          lsum[ks] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-          uint32_t wh[4], wl[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) split_p<T>(p[2 * u], p[2 * u + 1], wh[u], wl[u]);
-          phi[ks] = u32x4{wh[0], wh[1], wh[2], wh[3]};
-          plo[ks] = u32x4{wl[0], wl[1], wl[2], wl[3]};
-        }
-        l_run += lsum[0] + lsum[1];
-
-        // ---- O^T += V^T P^T (16-bit head and remainder of P) ----
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          if (kMasked && ks == 1 && nkeys < 32) break;
-          const VOps v = ks == 0 ? v0 : fetch_v(1);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            o[t] = Mma32<T>::mma(v.t[t], phi[ks], o[t]);
-            o[t] = Mma32<T>::mma(v.t[t], plo[ks], o[t]);
-          }
-        }
-      };
-      if (key0 + nkeys > lim_wave || nkeys < 32) unit(std::true_type{});
-      else unit(std::false_type{});
-      consumed += nslots;
-      cb += full ? 2 : 1;
+      sc = next;
+      if (moved) col.rescale(fast_exp2(shift));   // (unit i - 1's products, under the old reference, are in)
+      col.l += sum;
     }
+    stage(i + 2, std::integral_constant<int, kPfRing - 3>{});
   }
+  wait_loads<0>();   // no load may land after the workgroup has ended
+  products();
 
-  // ---- output: this lane holds dims 32t + 8u + 4h .. + 3 of its column ----
-  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-  const float l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-  if (col_ok) {
-    const float inv = 1.0f / l_tot;
-    const size_t row = ((size_t)(q0 + tq) * a.num_q_heads + (size_t)kvh * G + head) * kHeadDim;
+  const float inv = 1.0f / col.total();
+  if (col.ok) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const size_t idx = row + 32 * t + 8 * u + 4 * h;
-        store_pair<T>(a.out, idx, o[t][4 * u] * inv, o[t][4 * u + 1] * inv, a.out_fp32);
-        store_pair<T>(a.out, idx + 2, o[t][4 * u + 2] * inv, o[t][4 * u + 3] * inv, a.out_fp32);
-      }
+    for (int t = 0; t < 4; ++t) store_tile<T>(a, col.row, col.o[t], inv, t, h);
   }
 }
 
 template <typename T, int G, bool F8>
 hipError_t launch_typed(const PrefillArgs& a, bool elastic, hipStream_t st) {
   constexpr int kTileTok = kPfWaves * kPfCols / G;
-  dim3 grid((a.max_q_len + kTileTok - 1) / kTileTok, a.num_kv_heads, a.batch);
+  const int tiles = (a.max_q_len + kTileTok - 1) / kTileTok;
+  const dim3 grid((unsigned)tiles * a.num_kv_heads * a.batch);
   if (elastic) hipLaunchKernelGGL((prefill_kernel<T, G, true, F8>), grid, dim3(64 * kPfWaves), 0, st, a);
   else hipLaunchKernelGGL((prefill_kernel<T, G, false, F8>), grid, dim3(64 * kPfWaves), 0, st, a);
   return hipGetLastError();
