@@ -157,9 +157,10 @@ ekv_status ekv_lower(const uint8_t* h_tags, const int32_t* h_seq_lens, int32_t b
  * KV head)s that a launch cuts, two slots of G = num_q_heads / num_kv_heads
  * partial rows per workgroup of the persistent grid.  The size depends on
  * the group size and on the batch's work (number of sequences times its
- * length bound) only up to the grid's cap of 4096 workgroups, not on the
- * mode, the lengths themselves or the device: a workspace of this size
- * serves every call whose batch needs no more, on any device.  At most
+ * length bound: one workgroup per pair of blocks, up to the grid's cap of
+ * 4096 workgroups), not on the mode, the lengths themselves or the device: a
+ * workspace of this size serves every call whose batch needs no more, on any
+ * device.  At most
  * 2 * 4096 * G * 520 + 32 KiB bytes.  Returns 0 for unsupported shapes.
  */
 size_t ekv_decode_workspace_bytes(const ekv_pool* pool, const ekv_batch* batch);

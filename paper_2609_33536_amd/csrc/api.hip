@@ -83,13 +83,24 @@ int max_seq_blocks(const ekv_batch* b) {
   return (len + ekv::kPage - 1) / ekv::kPage;
 }
 
-// Fewest pairs (32 tokens) one workgroup streams; EKV_MIN_CHUNK overrides.
-int plan_min_chunk() {
+// Fewest pairs (32 tokens) one workgroup streams: 1 / 32 of the longest
+// sequence's pairs, at most 8.  A workgroup alone takes ~1.5 us a pair, so a
+// small batch is spread over the chip; but a merge reads 64 / G pieces per
+// memory round trip, so ranges far below 1 / 32 cost more in the merge than
+// they save in the stream.  Measured (bf16, 32 / 8 heads unless said; ranges of 1 / 2 /
+// this rule / 8 pairs, us): 4 sequences of 64-256 tokens, 8 / 2 heads 9.2 / 10.8 / 9.1 /
+// 19.3; 1 x 4096 17.6 / 12.4 / 11.5 (4 pairs) / 14.8; 8 x 512-2048 15.6 / 15.6 /
+// 15.6 / 19.5; 8-bit pool 4 x 1000-4000 21.8 / 19.0 / 16.9 / 19.1; from ~8192 tokens on the
+// rule gives 8, and from ~1024 ranges of 8 pairs in the batch on every launch
+// fills the chip and the rule has no effect.
+// EKV_MIN_CHUNK overrides.
+constexpr int kMostPairs = 8, kPieces = 32;
+int plan_min_chunk(int np_max) {
   if (const char* env = getenv("EKV_MIN_CHUNK")) {
     const int v = atoi(env);
     if (v > 0) return v;
   }
-  return 8;
+  return std::max(1, std::min(kMostPairs, (np_max + kPieces - 1) / kPieces));
 }
 
 // LDS ring depth of the decode kernel: the deepest ring that still lets 4
@@ -108,10 +119,12 @@ int decode_slots(const ekv_pool* p, int group, bool elastic) {
 // the launch (G rows a slot), the counters two per possible workgroup.
 // The launch grid is the kernel's resident workgroups on the device, or
 // fewer for small work, and never more than kMaxDecodeGrid.  The size a
-// caller allocates (exact = false) bounds the grid by the work and that cap
-// only, so it needs no device and serves every mode of a batch shape; the
-// size a call needs (exact = true) uses the device's own grid, the larger
-// of the native and the elastic kernel's.
+// caller allocates (exact = false) takes one pair a workgroup and that cap, so
+// it needs no device, serves every mode of a batch shape, and grows with the
+// batch's work whatever range length a call picks: a workspace made for the
+// largest batch serves every smaller one.  The size a call needs (exact =
+// true) uses the device's own grid, the larger of the native and the elastic
+// kernel's.
 struct DecodePlan {
   int min_chunk, grid;      // grid of the call's own mode (exact plans)
   long long pairs_max;
@@ -121,14 +134,13 @@ struct DecodePlan {
 ekv_status plan_decode(const ekv_pool* p, const ekv_batch* b, int group, bool exact, DecodePlan* d) {
   const int nblk = std::max(1, max_seq_blocks(b));
   const int np_max = (nblk + 1) / 2;
-  d->min_chunk = plan_min_chunk();
+  d->min_chunk = plan_min_chunk(np_max);
   d->pairs_max = (long long)b->batch * p->num_kv_heads * np_max;
   if (d->pairs_max >= (1LL << 30)) return fail(EKV_ERR_UNSUPPORTED, "batch too large for one decode call");
-  const long long wanted = (d->pairs_max + d->min_chunk - 1) / d->min_chunk;
   int grids[2] = {0, 0};
   for (int elastic = 0; elastic < 2; ++elastic) {
     if (!exact) {
-      grids[elastic] = (int)std::max<long long>(1, std::min<long long>(wanted, ekv::kMaxDecodeGrid));
+      grids[elastic] = (int)std::max<long long>(1, std::min<long long>(d->pairs_max, ekv::kMaxDecodeGrid));
       continue;
     }
     ekv::DecodeArgs a{};

@@ -319,14 +319,17 @@ __device__ __forceinline__ void pv_step(SplitState& st, const f32x4 (&s)[2], con
   else softmax_pv<T, 2>(st, s, o.v, tok0, lim, mask, c, g);
 }
 
-// After column-stacked accumulation: column n (< G) gets its remainder
-// column n + G added (lanes n and n + G of each 16-lane row).
+// After column-stacked accumulation: column n (< G) gets its remainder column
+// n + G added (lane n + G of the same 16-lane row, one shifted operand of the
+// add; the other lanes' results are not used).
 template <int G>
 __device__ __forceinline__ void stacked_sum(SplitState& st) {
 #pragma unroll
   for (int j = 0; j < 8; ++j)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) st.o[j][r] += __shfl_xor(st.o[j][r], G);
+    for (int r = 0; r < 4; ++r)
+      st.o[j][r] += __int_as_float(
+          __builtin_amdgcn_update_dpp(0, __float_as_int(st.o[j][r]), 0x100 + G, 0xf, 0xf, true));   // row_shl:G
 }
 
 template <typename T>

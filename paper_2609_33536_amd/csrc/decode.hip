@@ -48,6 +48,16 @@
 // (o, max, sum); the wave that finishes last -- found with a per-(sequence,
 // KV head) counter in the workspace -- merges them and writes the output,
 // then resets the counter to zero for the next call.
+//
+// A launch has a fixed cost that short batches are made of (4 sequences of
+// 64-256 tokens: 22.7 us before, 9.1 now; 1 x 4096: 18 -> 11.5; 24 x 513-2049, event
+// time 32.7 -> 28.7), paid in dependent memory round trips and in instruction
+// cache misses: every launch starts cold, and the kernel's path was 29-39 KB
+// of mostly straight-line code (25-28 misses per cache and launch by
+// SQC_ICACHE_MISSES).  So what runs once or rarely is compiled once (rolled
+// loops for the ring's issue, the first windows and the merge passes; 16-22 KB
+// now), scans and reductions are vector instructions instead of shuffles
+// through LDS, and positions divide in 32 bits.
 #include <algorithm>
 #include <atomic>
 
@@ -89,16 +99,27 @@ __device__ __forceinline__ float2 load_agent_f2(const float* p) {
   return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
 }
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-  return x;
+// Reductions over the lanes l with the same l % G (all of them get the
+// result): rotations inside the 16-lane rows, then across the rows.
+template <int N>
+__device__ __forceinline__ float row_ror(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xf, 0xf, true));
 }
-
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-  return x;
+template <int G>
+__device__ __forceinline__ float class_max(float x) {
+  if constexpr (G <= 8) x = fmaxf(x, row_ror<8>(x));
+  if constexpr (G <= 4) x = fmaxf(x, row_ror<4>(x));
+  if constexpr (G <= 2) x = fmaxf(x, row_ror<2>(x));
+  if constexpr (G <= 1) x = fmaxf(x, row_ror<1>(x));
+  return head_max(x);
+}
+template <int G>
+__device__ __forceinline__ float class_sum(float x) {
+  if constexpr (G <= 8) x += row_ror<8>(x);
+  if constexpr (G <= 4) x += row_ror<4>(x);
+  if constexpr (G <= 2) x += row_ror<2>(x);
+  if constexpr (G <= 1) x += row_ror<1>(x);
+  return head_sum(x);
 }
 
 // Workspace slots of partials.  Workgroup w owns slots 2w and 2w + 1: the
@@ -129,94 +150,74 @@ __device__ __forceinline__ int piece_slot(int w_first, int first_odd, int k) {
 __device__ __forceinline__ void store_agent_f4(float* p, f32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
 }
-__device__ __forceinline__ f32x4 load_agent_row4(const float* p) {
-  f32x4 v;
-  asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-  return v;
-}
-// Completes this wave's loads; the registers are tied to the wait so that no
-// use of them is scheduled before it.
-__device__ __forceinline__ void wait_rows(f32x4 (&v)[16]) {
-  asm volatile("s_waitcnt vmcnt(0)"
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
-                 "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15])
-               :
-               : "memory");
+// 16-byte loads with the same policy, through a buffer descriptor of the
+// partial rows (the compiler tracks them; its bound is the launch's slots).
+constexpr int kAgentScope = 16;   // the sc1 bit of the load's cache-policy operand
+__device__ __forceinline__ f32x4 load_agent_f4(__amdgpu_buffer_rsrc_t rows, uint32_t byte) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, byte, 0, kAgentScope));
 }
 
-// Merge the nsplit (<= 64) partials of the G heads of one (sequence, KV
-// head): out = sum_k w_k o_k / sum_k w_k l_k with w_k = exp2(m_k - max m).
-// Lane k holds split k's (max, sum).  The numerators follow the slot
-// layout: a load of the wave reads 64 consecutive chunks of one split (or,
-// for G = 1, the 32 chunks of two splits), so lane L owns head L % G and the
-// chunks L + 64 t.  The (max, sum) loads and the first 16 chunk loads are
-// issued together: a merge of up to one batch of splits costs one memory
-// round trip.
+// Merge the n partials of the G heads of one (sequence, KV head):
+// out = sum_k w_k o_k / sum_k w_k l_k with w_k = exp2(m_k - max m), in passes
+// of 64 / G pieces.  In a pass lane k G + h holds piece k's (max, sum) of head
+// h, and the row loads follow the slot layout: a load of the wave reads 64
+// consecutive chunks of one piece (or, for G = 1, the 32 chunks of two), so
+// lane L owns head L % G and the chunks L + 64 t.  A pass's loads are issued
+// together (32 of them, or 16 when they cover what is left): one memory round
+// trip for 64 / G pieces, whatever their number.  Passes after the first
+// rescale what they have to the new maximum.
 template <typename T, int G>
-__device__ void merge_splits(const DecodeArgs& a, size_t head0, int nsplit, int w_first, int first_odd, int lane) {
-  constexpr int kT = G >= 2 ? G / 2 : 1;        // loads per split (G = 1: one load covers two splits)
-  constexpr int kSB = G >= 2 ? 16 / kT : 32;    // splits per batch of 16 loads
-  float2 mlk[G];
-#pragma unroll
-  for (int h = 0; h < G; ++h)
-    mlk[h] = lane < nsplit ? load_agent_f2(a.ws_ml + 2 * ((size_t)piece_slot(w_first, first_odd, lane) * G + h))
-                           : make_float2(-__builtin_inff(), 0.f);
-  // split and chunk of load i of the batch at k0
-  auto split_of = [&](int k0, int i) { return G >= 2 ? k0 + i / kT : k0 + 2 * i + (lane >> 5); };
+__device__ __forceinline__ void merge_splits(const DecodeArgs& a, size_t head0, int n, int w_first, int first_odd, int lane) {
+  constexpr int kT = G >= 2 ? G / 2 : 1;        // loads per piece (G = 1: one load covers two pieces)
+  constexpr int kSB = G >= 2 ? 16 / kT : 32;    // pieces per 16 loads
+  constexpr int kPass = 64 / G;                 // = 2 kSB
+  constexpr uint32_t kSlotRows = G * kHeadDim * sizeof(float);
+  const auto rows = __builtin_amdgcn_make_buffer_rsrc(a.ws_o, 0, 2 * gridDim.x * kSlotRows, 0x00020000);
+  const int my_k = lane / G, my_h = lane % G;
   auto chunk_of = [&](int i) { return G >= 2 ? lane + 64 * (i % kT) : (lane & 31); };
-  f32x4 v[16];
-  auto load_batch = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int k = min(split_of(k0, i), nsplit - 1);   // a split that exists (zeroed below if past the last)
-      v[i] = load_agent_row4(a.ws_o + (size_t)piece_slot(w_first, first_odd, k) * G * kHeadDim + 4 * chunk_of(i));
-    }
-  };
-  load_batch(0);
-  const int my_h = lane % G;
-  float wk[G], my_inv = 0.f;
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    const float mmax = wave_max(mlk[h].x);
-    wk[h] = lane < nsplit ? fast_exp2(mlk[h].x - mmax) : 0.f;
-    const float inv = 1.0f / wave_sum(wk[h] * mlk[h].y);
-    my_inv = h == my_h ? inv : my_inv;
-  }
+  float mmax = -__builtin_inff(), den = 0.f;
   f32x4 num[kT];
 #pragma unroll
   for (int t = 0; t < kT; ++t) num[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0;;) {
-    wait_rows(v);
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (split_of(k0, i) >= nsplit) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (G >= 2) {
-#pragma unroll
-      for (int sp = 0; sp < kSB; ++sp) {
-        const int k = min(k0 + sp, 63);
-        float w = 0.f;
-#pragma unroll
-        for (int h = 0; h < G; ++h) {
-          const float wh = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wk[h]), k));
-          w = h == my_h ? wh : w;
-        }
-#pragma unroll
-        for (int t = 0; t < kT; ++t) num[t] += w * v[sp * kT + t];
-      }
-    } else {
+#pragma unroll 1
+  for (int k0 = 0; k0 < n; k0 += kPass) {
+    const float2 ml = k0 + my_k < n
+                          ? load_agent_f2(a.ws_ml + 2 * ((size_t)piece_slot(w_first, first_odd, k0 + my_k) * G + my_h))
+                          : make_float2(-__builtin_inff(), 0.f);
+    f32x4 v[2][16];
+    auto load_half = [&](int half) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const int k = k0 + 2 * i;
-        const float w0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wk[0]), min(k, 63)));
-        const float w1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wk[0]), min(k + 1, 63)));
-        num[0] += ((lane >> 5) ? w1 : w0) * v[i];
+        const int k = k0 + half * kSB + (G >= 2 ? i / kT : 2 * i + (lane >> 5));
+        // (past the last piece: beyond the descriptor's bound, which reads zeros and no memory)
+        const uint32_t slot = k < n ? (uint32_t)piece_slot(w_first, first_odd, k) * kSlotRows : 0x80000000u;
+        v[half][i] = load_agent_f4(rows, slot + 16 * chunk_of(i));
       }
+    };
+    const bool both = n - k0 > kSB;
+    load_half(0);
+    if (both) load_half(1);
+    const float top = fmaxf(mmax, class_max<G>(ml.x));
+    const float w = k0 + my_k < n ? fast_exp2(ml.x - top) : 0.f;
+    if (k0 > 0) {
+      const float f = fast_exp2(mmax - top);
+      den *= f;
+#pragma unroll
+      for (int t = 0; t < kT; ++t) num[t] *= f;
     }
-    k0 += kSB;
-    if (k0 >= nsplit) break;
-    load_batch(k0);
+    mmax = top;
+    den += w * ml.y;
+    auto add_half = [&](int half) {   // (a piece past the last: weight 0, rows 0)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int k = half * kSB + (G >= 2 ? i / kT : 2 * i + (lane >> 5));
+        num[i % kT] += __shfl(w, k * G + my_h) * v[half][i];
+      }
+    };
+    add_half(0);
+    if (both) add_half(1);
   }
-  if constexpr (G == 1) {   // the two halves of the wave summed splits of opposite parity
+  if constexpr (G == 1) {   // the two halves of the wave summed pieces of opposite parity
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(num[0][e]), __float_as_uint(num[0][e]),
@@ -224,49 +225,18 @@ __device__ void merge_splits(const DecodeArgs& a, size_t head0, int nsplit, int 
       num[0][e] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     }
   }
+  const float inv = 1.0f / class_sum<G>(den);
   if (G >= 2 || lane < 32) {
 #pragma unroll
     for (int t = 0; t < kT; ++t) {
       const int q = chunk_of(t);
       const int ci = q / (4 * G), g = (q % (4 * G)) / G;
-      const f32x4 tot = num[t] * my_inv;
+      const f32x4 tot = num[t] * inv;
       const size_t idx = (head0 + my_h) * kHeadDim + 32 * g + 4 * ci;
       store_pair<T>(a.out, idx, tot[0], tot[1], a.out_fp32);
       store_pair<T>(a.out, idx + 2, tot[2], tot[3], a.out_fp32);
     }
   }
-}
-
-// Any number of splits, one head (h of the group) at a time (long sequences only).
-template <typename T, int G>
-__device__ void merge_head_serial(const DecodeArgs& a, size_t head, int h, int nsplit, int w_first, int first_odd,
-                                  int lane) {
-  const float* ml = a.ws_ml + 2 * h;
-  // dims 2 lane, 2 lane + 1: chunk (c % 8) * 4G + h + G (c / 8) of the slot, c = lane / 2
-  const int c = lane >> 1;
-  const float* o = a.ws_o + 4 * ((c & 7) * 4 * G + h + G * (c >> 3)) + 2 * (lane & 1);
-  float mmax = -__builtin_inff();
-  for (int k0 = 0; k0 < nsplit; k0 += 64)
-    if (k0 + lane < nsplit) mmax = fmaxf(mmax, load_agent_f2(ml + 2 * (size_t)piece_slot(w_first, first_odd, k0 + lane) * G).x);
-  mmax = wave_max(mmax);
-  float den = 0.f, num0 = 0.f, num1 = 0.f;
-  for (int k0 = 0; k0 < nsplit; k0 += 64) {
-    float wk = 0.f;
-    if (k0 + lane < nsplit) {
-      const float2 mlk = load_agent_f2(ml + 2 * (size_t)piece_slot(w_first, first_odd, k0 + lane) * G);
-      wk = fast_exp2(mlk.x - mmax);
-      den += wk * mlk.y;
-    }
-    const int kn = min(64, nsplit - k0);
-    for (int k = 0; k < kn; ++k) {
-      const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wk), k));
-      const float2 v = load_agent_f2(o + (size_t)piece_slot(w_first, first_odd, k0 + k) * G * kHeadDim);
-      num0 += w * v.x;
-      num1 += w * v.y;
-    }
-  }
-  const float inv = 1.0f / wave_sum(den);
-  store_pair<T>(a.out, head * kHeadDim + 2 * lane, num0 * inv, num1 * inv, a.out_fp32);
 }
 
 // Wait until at most n load/store instructions of this wave are in flight
@@ -432,18 +402,16 @@ __device__ __forceinline__ u32x2 nib_v_operand(const NibPlanes (&p)[4], int j) {
   return u32x2{perm(p[1].even, p[0].even, sel), perm(p[3].even, p[2].even, sel)};
 }
 
-__device__ __forceinline__ int wave_sum_int(int x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-  return x;
-}
-
-__device__ __forceinline__ int wave_incl_scan(int x, int lane) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(x, off);
-    if (lane >= off) x += y;
-  }
+// Inclusive scan over the wave's 64 lanes in vector instructions (row shifts,
+// then the row totals broadcast into the rows after them): 6 dependent adds,
+// where a shuffle through LDS pays a round trip per step.
+__device__ __forceinline__ int wave_incl_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);    // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);    // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);    // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);    // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
   return x;
 }
 
@@ -514,16 +482,19 @@ __global__ __launch_bounds__(64) void decode_kernel(DecodeArgs a) {
 
   // ---- the range of this workgroup -------------------------------------
   const int len0 = lane < B ? clamp_len(a.seq_lens[lane], a.len_cap) : 0;   // kept: sequences 0..63
-  int total_pairs = 0;
-  for (int c0 = 0; c0 < B; c0 += 512) {
-    int np8[8];
+  const int incl0 = wave_incl_scan(pairs_of(len0));
+  int total_pairs = __builtin_amdgcn_readlane(incl0, 63);
+  if (B > 64) {   // each lane adds up its share of the rest (8 loads in flight), one reduction at the end
+    int rest = 0;
+#pragma unroll 1
+    for (int c0 = 64; c0 < B; c0 += 512) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int idx = c0 + 64 * u + lane;
-      np8[u] = pairs_of(idx < 64 ? len0 : (idx < B ? clamp_len(a.seq_lens[idx], a.len_cap) : 0));
+      for (int u = 0; u < 8; ++u) {
+        const int idx = c0 + 64 * u + lane;
+        rest += pairs_of(idx < B ? clamp_len(a.seq_lens[idx], a.len_cap) : 0);
+      }
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) total_pairs += __builtin_amdgcn_readfirstlane(wave_sum_int(np8[u]));
+    total_pairs += __builtin_amdgcn_readlane(wave_incl_scan(rest), 63);
   }
   const int T_all = hkv * total_pairs;
   if (blockIdx.x == 0) {   // empty sequences: zero output
@@ -539,34 +510,36 @@ __global__ __launch_bounds__(64) void decode_kernel(DecodeArgs a) {
     }
   }
   // Ranges: `heavy` leading workgroups stream r_heavy pairs each, the others r_light
-  // (equal ranges when heavy is 0 or the work is at the minimum range).
-  const int grid = (int)gridDim.x;
-  int r_heavy = max(a.min_chunk, (T_all + grid - 1) / grid), r_light = r_heavy, heavy = 0;
-  if (a.heavy > 0 && a.heavy < grid && (T_all + grid - 1) / grid > a.min_chunk) {
+  // (equal ranges when heavy is 0 or the work is at the minimum range).  T_all is
+  // below 2^30 and the weight below 2, so every offset fits 32 bits unsigned.
+  const uint32_t grid = gridDim.x;
+  const uint32_t mean = ((uint32_t)T_all + grid - 1) / grid;
+  uint32_t r_heavy = max((uint32_t)a.min_chunk, mean), r_light = r_heavy, heavy = 0;
+  if (a.heavy > 0 && (uint32_t)a.heavy < grid && mean > (uint32_t)a.min_chunk) {
     heavy = a.heavy;
-    r_heavy = max(1, (int)(((long long)T_all * a.heavy_permille + 1000LL * grid - 1) / (1000LL * grid)));
-    const long long rest = (long long)T_all - (long long)heavy * r_heavy;
-    r_light = rest > 0 ? (int)((rest + (grid - heavy) - 1) / (grid - heavy)) : 1;
+    r_heavy = max(1u, (uint32_t)(((uint64_t)T_all * a.heavy_permille + 1000ull * grid - 1) / (1000ull * grid)));
+    const int64_t rest = (int64_t)T_all - (int64_t)((uint64_t)heavy * r_heavy);
+    r_light = rest > 0 ? ((uint32_t)rest + (grid - heavy) - 1) / (grid - heavy) : 1u;
   }
-  const long long heavy_end = (long long)heavy * r_heavy;
-  auto range_start = [&](int w) -> long long {
-    return w < heavy ? (long long)w * r_heavy : heavy_end + (long long)(w - heavy) * r_light;
+  const uint32_t heavy_end = heavy * r_heavy;
+  auto range_start = [&](uint32_t w) -> uint32_t { return w < heavy ? w * r_heavy : heavy_end + (w - heavy) * r_light; };
+  auto range_of = [&](uint32_t pos) -> int {   // the workgroup whose range holds pair pos
+    const bool lead = pos < heavy_end;
+    return (int)((lead ? 0u : heavy) + (pos - (lead ? 0u : heavy_end)) / (lead ? r_heavy : r_light));
   };
-  auto range_of = [&](int pos) -> int {   // the workgroup whose range holds pair pos
-    return pos < heavy_end ? pos / r_heavy : heavy + (int)((pos - heavy_end) / r_light);
-  };
-  if (range_start((int)blockIdx.x) >= T_all) return;
-  const int start = (int)range_start((int)blockIdx.x);
-  const int end = (int)min((long long)T_all, range_start((int)blockIdx.x + 1));
+  if (range_start(blockIdx.x) >= (uint32_t)T_all) return;
+  const int start = (int)range_start(blockIdx.x);
+  const int end = (int)min((uint32_t)T_all, range_start(blockIdx.x + 1));
 
   Walker w0;
   {
     int cum = 0;
+#pragma unroll 1
     for (int c0 = 0;; c0 += 64) {
       const int idx = c0 + lane;
       const int len = c0 == 0 ? len0 : (idx < B ? clamp_len(a.seq_lens[idx], a.len_cap) : 0);
       const int np = pairs_of(len);
-      const int incl = wave_incl_scan(np, lane);
+      const int incl = c0 == 0 ? incl0 : wave_incl_scan(np);
       const uint64_t hit = __builtin_amdgcn_ballot_w64(hkv * (cum + incl) > start);
       if (hit) {
         const int l0 = __builtin_ctzll(hit);
@@ -582,7 +555,7 @@ __global__ __launch_bounds__(64) void decode_kernel(DecodeArgs a) {
     }
     w0.nblk = (w0.len + kPage - 1) / kPage;
     const int off = start - w0.seq_base;
-    w0.kvh = off / w0.np;
+    w0.kvh = (int)((uint32_t)off / (uint32_t)w0.np);
     w0.j = off - w0.kvh * w0.np;
     w0.g = start;
   }
@@ -755,18 +728,25 @@ __global__ __launch_bounds__(64) void decode_kernel(DecodeArgs a) {
   const size_t v_off = (size_t)hkv * kTile;
 
   // ---- issue side ------------------------------------------------------
-  Walker iwk = w0;
-  Window icur = next_window(iwk);
-  dma_window(icur, 0);
-  const int ops_w0 = ops;
-  bool i_has_next = iwk.g < end;
-  Window inext = icur;
-  int ops_inext = 0;
-  if (i_has_next) {
+  // The first two windows' metadata is requested together (one copy of the
+  // code: the walk, the loads and the issue below are each compiled once, since
+  // a launch starts with a cold instruction cache and short ranges pay for
+  // every line of straight-line code).
+  Walker iwk = w0, cwk = w0;
+  Window icur, inext;
+  int ops_w0 = 0;
+#pragma unroll 1
+  for (int k = 0; k < 2 && iwk.g < end; ++k) {
     inext = next_window(iwk);
-    dma_window(inext, 1);
-    ops_inext = ops;
+    dma_window(inext, k);
+    if (k == 0) {
+      icur = inext;
+      cwk = iwk;
+      ops_w0 = ops;
+    }
   }
+  bool i_has_next = cwk.g < end;
+  int ops_inext = ops;
   const int ops_prologue = ops;
   int iw_idx = 0;
   wait_vm<NSLOT - 1>(ops - ops_w0);
@@ -863,8 +843,7 @@ __global__ __launch_bounds__(64) void decode_kernel(DecodeArgs a) {
   };
 
   // ---- consume side ----------------------------------------------------
-  Walker cwk = w0;
-  Window ccur = next_window(cwk);
+  Window ccur = icur;
   int cw_idx = 0;
   int c_ops = ops_prologue;     // instructions issued up to and including the slot being consumed
   int ctag = 0;
@@ -949,7 +928,7 @@ __global__ __launch_bounds__(64) void decode_kernel(DecodeArgs a) {
       }
       pend_head0[pend_n] = head0;
       pend_wfirst[pend_n] = w_first;
-      pend_odd[pend_n] = first > range_start(w_first) ? 1 : 0;
+      pend_odd[pend_n] = (uint32_t)first > range_start(w_first) ? 1 : 0;
       pend_pieces[pend_n] = pieces;
       ++pend_n;
     }
@@ -959,13 +938,15 @@ __global__ __launch_bounds__(64) void decode_kernel(DecodeArgs a) {
   auto ring_has_room = [&]() {
     return F8 ? n_issued - n_consumed + 2 <= 2 * NSLOT : n_issued - n_consumed < NSLOT;
   };
-#pragma unroll
+  // (both loops rolled; a single loop until the ring is full, here and below,
+  // measured 1 % slower on the 70B layer, 484 against 477 us)
+#pragma unroll 1
   for (int k = 0; k < (F8 ? 2 * NSLOT - 2 : NSLOT - 1); ++k)
     if (!issue_done && ring_has_room()) issue_slot();
 
   while (true) {
     // keep the ring full
-#pragma unroll
+#pragma unroll 1
     for (int u = 0; u < 2; ++u)
       if (!issue_done && ring_has_room()) issue_slot();
     if constexpr (F8) {
@@ -1173,15 +1154,15 @@ __global__ __launch_bounds__(64) void decode_kernel(DecodeArgs a) {
       prev1 = __hip_atomic_fetch_add(a.counters + piece_slot(pend_wfirst[1], pend_odd[1], 0), 1u, __ATOMIC_RELAXED,
                                      __HIP_MEMORY_SCOPE_AGENT);
   }
+#pragma unroll 1
   for (int k = 0; k < pend_n; ++k) {
-    uint32_t* counter = a.counters + piece_slot(pend_wfirst[k], pend_odd[k], 0);
-    if (__builtin_amdgcn_readfirstlane(k == 0 ? prev0 : prev1) != (uint32_t)(pend_pieces[k] - 1)) continue;
+    const int w_first = k == 0 ? pend_wfirst[0] : pend_wfirst[1], odd = k == 0 ? pend_odd[0] : pend_odd[1];
+    const int pieces = k == 0 ? pend_pieces[0] : pend_pieces[1];
+    if (__builtin_amdgcn_readfirstlane(k == 0 ? prev0 : prev1) != (uint32_t)(pieces - 1)) continue;
     asm volatile("" ::: "memory");
-    if (lane == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (pend_pieces[k] <= 64) merge_splits<T, G>(a, pend_head0[k], pend_pieces[k], pend_wfirst[k], pend_odd[k], lane);
-    else
-      for (int h = 0; h < G; ++h)
-        merge_head_serial<T, G>(a, pend_head0[k] + h, h, pend_pieces[k], pend_wfirst[k], pend_odd[k], lane);
+    if (lane == 0)
+      __hip_atomic_store(a.counters + piece_slot(w_first, odd, 0), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    merge_splits<T, G>(a, k == 0 ? pend_head0[0] : pend_head0[1], pieces, w_first, odd, lane);
   }
   EKV_TL(tl_write();)
 }

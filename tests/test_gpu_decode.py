@@ -238,3 +238,31 @@ def test_decode_batch_of_700_short_sequences(dtype):
         test_gpu_fp8._run_decode(c, 8, 2)
     else:
         _run(c, 8, 2)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "e5m2"])
+@pytest.mark.parametrize("group", [1, 4, 8, 16])
+def test_decode_merge_pass_edges(group, dtype, monkeypatch):
+    """One-pair ranges, so a (sequence, KV head) of n pairs is merged from n
+    pieces: one piece fewer, as many and one more than half a merge pass
+    (32 / group pieces), a whole pass and two passes."""
+    monkeypatch.setenv("EKV_MIN_CHUNK", "1")
+    half = 32 // group
+    pieces = sorted({n for k in (1, 2, 4) for n in (k * half - 1, k * half, k * half + 1) if n > 0})
+    lens = [32 * n - 5 * (n % 3) for n in pieces]
+    c = workloads.make_decode_case(lens, 2 * group, 2, seed=300 + group, base_fraction=0.5, spare_blocks=2, dtype=dtype)
+    if dtype == "e5m2":
+        from tests import test_gpu_fp8
+        test_gpu_fp8._run_decode(c, 2 * group, 2)
+    else:
+        _run(c, 2 * group, 2)
+
+
+@pytest.mark.parametrize("longest", [1024, 1025, 2080, 7168, 7169, 8200, 40000])
+def test_decode_range_rule_edges(longest):
+    """The default range length follows the longest sequence (ceil(pairs / 32),
+    at most 8): lengths around its steps, with one, a few and many sequences."""
+    for batch in (1, 3, 70 if longest < 3000 else 5):
+        lens = [longest] + [1 + (37 * s * s) % min(longest, 1500) for s in range(1, batch)]
+        c = workloads.make_decode_case(lens, 8, 2, seed=310 + batch, base_fraction=0.3, spare_blocks=2)
+        _run(c, 8, 2)
