@@ -81,3 +81,11 @@ def test_layers_argument_errors():
         ekv.demote_layers(pool, empty, pairs, bt, tags, freed)       # no layers
     torch.cuda.synchronize()
     assert np.array_equal(dev.cpu().numpy().view(np.uint16), case["pool"])   # nothing was enqueued
+
+
+@pytest.mark.parametrize("num_layers,hkv", [(33, 1), (24, 8)])
+def test_commit_beside_data_over_many_waves(num_layers, hkv):
+    """The table updates are made in the data launch: 2 tiles a layer, and more
+    workgroups than the chip holds at once (so that tiles run before and after
+    the update of their pair)."""
+    test_demote_refine_all_layers(num_layers, hkv)
