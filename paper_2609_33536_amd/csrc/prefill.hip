@@ -4,7 +4,7 @@
 // itself).
 //
 // A workgroup of 4 waves serves one (sequence, KV head, tile of query
-// tokens); a wave owns 32 query "columns" -- (token, head-in-group) pairs.
+// tokens); a wave works on 32 query "columns" -- (token, head-in-group) pairs.
 // The work unit is one pair of blocks, 32 keys (the missing second block of
 // a lone last one is masked).  On 32x32x16 matrix cores, per unit:
 //   S^T (32 keys x 32 columns) = K (32 x 128) . Q^T, 8 products;
@@ -28,6 +28,11 @@
 // the quarter that it loaded).  When every wave fetched and widened the BASE
 // operands for itself, a unit cost a wave 182 vector, 110 scalar and 21 branch
 // instructions; now ~140, ~55 and ~8.
+//
+// Two kernels:
+//   prefill_kernel        4 waves x 32 columns share every unit;
+//   prefill_split_kernel  4 waves share 32 columns and take every fourth unit
+//                         each: small launches, which leave most CUs idle.
 #include <type_traits>
 
 #include "attn_device.h"
@@ -441,6 +446,24 @@ struct Extent {
   __device__ __forceinline__ int seen(int t) const { return max(1, min(len, len - nq + t + 1)); }
 };
 
+// Workgroup -> (sequence, KV head), query tile; the last tiles (most keys)
+// first.  Ids go round robin over the 8 XCDs: with a multiple of 8 KV heads
+// all tiles of one (sequence, KV head) go to one XCD and share its L2, and
+// every XCD gets a KV head of every sequence; otherwise whole (sequence, KV
+// head)s would load the XCDs unevenly (12 of them: 1.4x the time), and the
+// tiles are spread instead.
+__device__ __forceinline__ void place(const PrefillArgs& a, int tiles, int* grp, int* tile) {
+  if (a.num_kv_heads % 8 == 0) {
+    const int i = blockIdx.x >> 3;
+    *grp = 8 * (i / tiles) + (blockIdx.x & 7);
+    *tile = tiles - 1 - i % tiles;
+  } else {
+    const int groups = a.batch * a.num_kv_heads;
+    *grp = blockIdx.x % groups;
+    *tile = tiles - 1 - blockIdx.x / groups;
+  }
+}
+
 // ---- 4 waves x 32 columns over shared units --------------------------------
 // Software pipeline, one barrier a unit: the body of unit i runs the softmax of
 // unit i while the matrix cores run the P.V products of unit i - 1 and the
@@ -468,22 +491,8 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
   __shared__ __attribute__((aligned(16))) char ring[kPfRing * kSlotPf];
   constexpr int kTileTok = kPfWaves * kPfCols / G;
   const int tiles = (a.max_q_len + kTileTok - 1) / kTileTok;
-  // Workgroup -> (sequence, KV head), query tile; the last tiles (most keys)
-  // first.  Ids go round robin over the 8 XCDs: with a multiple of 8 KV heads
-  // all tiles of one (sequence, KV head) go to one XCD and share its L2, and
-  // every XCD gets a KV head of every sequence; otherwise whole (sequence, KV
-  // head)s would load the XCDs unevenly (12 of them: 1.4x the time), and the
-  // tiles are spread instead.
-  const int groups = a.batch * a.num_kv_heads;
   int grp, tile;
-  if (a.num_kv_heads % 8 == 0) {
-    const int i = blockIdx.x >> 3;
-    grp = 8 * (i / tiles) + (blockIdx.x & 7);
-    tile = tiles - 1 - i % tiles;
-  } else {
-    grp = blockIdx.x % groups;
-    tile = tiles - 1 - blockIdx.x / groups;
-  }
+  place(a, tiles, &grp, &tile);
   const int s = grp / a.num_kv_heads, kvh = grp % a.num_kv_heads;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, h = lane >> 5;
@@ -579,8 +588,136 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
   }
 }
 
+// ---- 4 waves share 32 columns and divide the units --------------------------
+// A small chunk gives few workgroups of 128 columns, each a serial chain over
+// its units (~0.7 us a unit, two LDS round trips, the matrix chain and the
+// softmax among them) while most CUs idle.  Here a workgroup has 32 columns and
+// wave w takes units w, w + 4, ...: a quarter of the chain, four times the
+// workgroups.  A wave loads and widens its units alone (two slots of its own,
+// no barrier in the loop); the waves' (o, m, l) are merged through LDS.
+// Three fp16 prompts of 17-130 tokens over prefixes of up to 700: 28.8 -> 17.2 us;
+// one 4715-token context + 3 rows, 32 / 8 heads: 92 -> 43.
+template <typename T, int G, bool ELASTIC, bool F8>
+__global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(1, 1))) void prefill_split_kernel(PrefillArgs a) {
+  __shared__ __attribute__((aligned(16))) char ring[kPfWaves * 2 * kSlotPf];
+  constexpr int kTileTok = kPfCols / G;
+  const int tiles = (a.max_q_len + kTileTok - 1) / kTileTok;
+  int grp, tile;
+  place(a, tiles, &grp, &tile);
+  const int s = grp / a.num_kv_heads, kvh = grp % a.num_kv_heads;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, h = lane >> 5;
+  const Extent x(a, s);
+  const int t_begin = tile * kTileTok;
+  if (t_begin >= x.nq) return;   // uniform over the workgroup
+
+  Columns<T, G> col(a, kvh, x.q0, x.nq, x.len, t_begin * G, lane);
+  const int nblk = (x.seen(min(x.nq, t_begin + kTileTok) - 1) + kPage - 1) / kPage;
+  PairTable<ELASTIC, F8> table(a, s, kvh, nblk, lane);
+  const int units = table.units;
+  const int valid = min(x.len, nblk * kPage);   // V rows of keys at or past this are zeroed
+  const Stager<F8> stager(lane, a.num_kv_heads);
+  char* own = ring + wave * 2 * kSlotPf;
+  const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr)own);
+  const uint32_t k_at = k_read_offset(lane), v_at = v_read_offset(lane);
+  constexpr int kUnitLoads = 4 * Stager<F8>::kLoads;
+
+  bool base_of[2] = {false, false};   // the units in slots 0 and 1
+  auto issue = [&](int u, int slot) {
+    const bool base = table.seek(u, lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) stager.load(table.tile(u, q >> 1), base, q, lds + slot * kSlotPf);
+    base_of[slot] = base;
+  };
+  auto unit = [&](int u, int slot) {
+    char* at = own + slot * kSlotPf;
+    if (u + kPfWaves < units) wait_loads<kUnitLoads>();
+    else wait_loads<0>();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) stager.widen(at, base_of[slot], q, 32 * u, valid, lane);
+    u32x4 k[8], v[2][4], hi[2], lo[2];
+    read_k(at + k_at, k);
+    read_v(at + v_at, v);
+    f32x16 sc = col.scores(k);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slot has been read
+    if (u + 2 * kPfWaves < units) issue(u + 2 * kPfWaves, slot);
+    const float c = col.mask(sc, 32 * u, h);
+    float shift;
+    // (columns that see none of this wave's keys yet keep the reference -inf)
+    if (col.advance(sc, c, &shift)) col.rescale(shift == shift ? fast_exp2(shift) : 1.0f);
+    col.l += col.probabilities(sc, c, col.m == -__builtin_inff() ? 0.f : col.m, hi, lo);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      col.accumulate(v[ks], hi[ks]);
+      col.accumulate(v[ks], lo[ks]);
+    }
+  };
+  if (wave < units) issue(wave, 0);
+  if (wave + kPfWaves < units) issue(wave + kPfWaves, 1);
+#pragma unroll 1
+  for (int u = wave; u < units; u += 2 * kPfWaves) {
+    unit(u, 0);
+    if (u + kPfWaves < units) unit(u + kPfWaves, 1);
+  }
+
+  // ---- merge: wave w sums dim tile w of the four waves ----
+  const float l = col.total();
+  barrier();   // every wave is done with the slots (its last loads have been waited for)
+  f32x4* parts = reinterpret_cast<f32x4*>(ring);                                  // [wave][tile][4][lane]
+  float2* ml = reinterpret_cast<float2*>(ring + kPfWaves * 16 * 64 * sizeof(f32x4));   // [wave][lane]
+  ml[64 * wave + lane] = make_float2(col.m, l);
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      parts[((wave * 4 + t) * 4 + r) * 64 + lane] =
+          f32x4{col.o[t][4 * r], col.o[t][4 * r + 1], col.o[t][4 * r + 2], col.o[t][4 * r + 3]};
+  barrier();
+  float2 m[kPfWaves];
+  float top = -__builtin_inff(), sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < kPfWaves; ++w) {
+    m[w] = ml[64 * w + lane];
+    top = fmaxf(top, m[w].x);
+  }
+  f32x16 o = f32x16{};
+#pragma unroll
+  for (int w = 0; w < kPfWaves; ++w) {
+    const float f = fast_exp2(m[w].x - top);
+    sum += f * m[w].y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const f32x4 p = parts[((w * 4 + wave) * 4 + r) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[4 * r + e] += f * p[e];
+    }
+  }
+  if (col.ok) store_tile<T>(a, col.row, o, 1.0f / sum, wave, h);
+}
+
+// Whether a launch that would have `workgroups` workgroups of 32 columns uses
+// prefill_split_kernel: if they fit the 256 CUs at once (one a CU), or
+// twice that over contexts of at least 512 keys, where a quarter of the chain
+// saves more than the second round's start and merge cost.  Measured (us with
+// the append, 128-column / split kernel): 8 workgroups, 4715 + 3 keys 92 / 43;
+// 208, 4322 + 412 139 / 69; 240, 7368 + 18 173 / 75; 384, 3750 + 61 78 / 54; 408, 700 + 130
+// 28.8 / 17.2; beyond the line 320, 182 + 45 16.7 / 18.9; 720, 523 + 236 31.4 / 36.6;
+// 1088, 539 20.6 / 24.0; 16384 (the 8B chunked prefill) 481 / 948.
+constexpr int kChipCus = 256;
+bool divide_units(int64_t workgroups, int max_len) {
+  return workgroups <= kChipCus || (workgroups <= 2 * kChipCus && max_len >= 512);
+}
+
 template <typename T, int G, bool F8>
 hipError_t launch_typed(const PrefillArgs& a, bool elastic, hipStream_t st) {
+  constexpr int kSplitTok = kPfCols / G;
+  const int64_t split = (int64_t)((a.max_q_len + kSplitTok - 1) / kSplitTok) * a.num_kv_heads * a.batch;
+  if (divide_units(split, a.max_len)) {
+    const dim3 grid((unsigned)split);
+    if (elastic) hipLaunchKernelGGL((prefill_split_kernel<T, G, true, F8>), grid, dim3(64 * kPfWaves), 0, st, a);
+    else hipLaunchKernelGGL((prefill_split_kernel<T, G, false, F8>), grid, dim3(64 * kPfWaves), 0, st, a);
+    return hipGetLastError();
+  }
   constexpr int kTileTok = kPfWaves * kPfCols / G;
   const int tiles = (a.max_q_len + kTileTok - 1) / kTileTok;
   const dim3 grid((unsigned)tiles * a.num_kv_heads * a.batch);

@@ -1,10 +1,11 @@
 """Chunked prefill at the edges of its tiles, units, ring and metadata windows,
 against the float64 oracle (tolerance as in the other prefill tests)."""
 
+import numpy as np
 import pytest
 
 from paper_2609_33536_amd import workloads
-from tests import test_gpu_fp8, test_gpu_prefill
+from tests import softmax_rises, test_gpu_fp8, test_gpu_prefill
 
 pytestmark = pytest.mark.gpu
 
@@ -16,28 +17,65 @@ def _run(case, hq, hkv, **kw):
         test_gpu_prefill._run_prefill(case, hq, hkv, **kw)
 
 
+def _routed(prefix, chunk, group, hkv, split):
+    """The sequences in batches of one kernel: for the unit-dividing one, as many
+    as keep its 32-column workgroups within 256; for the other, all of them and
+    one-token prompts until there are more than 512."""
+    tiles = -(-max(chunk) * group // 32)
+    if split:
+        per = max(1, 256 // (tiles * hkv))
+        return [(prefix[i:i + per], chunk[i:i + per]) for i in range(0, len(chunk), per)]
+    pad = max(0, 512 // (tiles * hkv) + 1 - len(chunk))
+    return [(prefix + [0] * pad, chunk + [1] * pad)]
+
+
+@pytest.mark.parametrize("split", [True, False])
 @pytest.mark.parametrize("dtype", ["bf16", "fp16", "e5m2"])
 @pytest.mark.parametrize("group,hkv", [(4, 8), (16, 3), (1, 2)])
-def test_prefill_tile_unit_and_ring_edges(group, hkv, dtype):
+def test_prefill_tile_unit_and_ring_edges(group, hkv, dtype, split):
     """Chunks one row below, at and above a query tile (128 / group tokens) and
     a wave's columns; contexts of 1 .. 6 units (32 keys) and one key around a
-    unit, with whole, lone and partly filled last blocks; BASE and TARGET units
-    mixed.  8 KV heads take the one-XCD-per-head order of the workgroups, 3 and
-    2 the other."""
+    unit, with whole, lone and partly filled last blocks, and waves without a
+    unit or with only masked ones; BASE and TARGET units mixed.  8 KV heads take
+    the one-XCD-per-head order of the workgroups, 3 and 2 the other."""
     tile = 128 // group
     prefix = [0, 0, 0, 1, 15, 16, 31, 32, 33, 47, 64, 96, 128, 160]
     chunk = [1, tile, tile + 1, tile - 1 or 1, 1, 16, 1, 2, 31, 1, 32, tile, 33, 1]
-    c = workloads.make_prefill_case(prefix, chunk, group * hkv, hkv, dtype=dtype, seed=211, base_fraction=0.6,
-                                    spare_blocks=2)
-    _run(c, group * hkv, hkv)
+    for k, (p, c) in enumerate(_routed(prefix, chunk, group, hkv, split)):
+        case = workloads.make_prefill_case(p, c, group * hkv, hkv, dtype=dtype, seed=211 + k, base_fraction=0.6,
+                                           spare_blocks=2)
+        _run(case, group * hkv, hkv)
 
 
+@pytest.mark.parametrize("split", [True, False])
 @pytest.mark.parametrize("dtype", ["bf16", "e5m2"])
 @pytest.mark.parametrize("placement", ["random", "oldest"])
-def test_prefill_metadata_window_edges(placement, dtype):
+def test_prefill_metadata_window_edges(placement, dtype, split):
     """Contexts that end one block before, at and after the 64-pair (2048-token)
     windows of the block table."""
-    c = workloads.make_prefill_case([2016, 2030, 2048, 2049, 4095], [16, 18, 1, 31, 2], 8, 2, dtype=dtype, seed=212,
-                                    base_fraction=0.5, placement=placement, spare_blocks=2)
-    _run(c, 8, 2)
-    _run(c, 8, 2, use_boundaries=False)
+    for p, c in _routed([2016, 2030, 2048, 2049, 4095], [16, 18, 1, 31, 2], 4, 2, split):
+        case = workloads.make_prefill_case(p, c, 8, 2, dtype=dtype, seed=212, base_fraction=0.5, placement=placement,
+                                           spare_blocks=2)
+        _run(case, 8, 2)
+        _run(case, 8, 2, use_boundaries=False)
+
+
+@pytest.mark.parametrize("name", ["aligned-bf16", "scale1-bf16-g16", "aligned-e5m2"])
+def test_prefill_rescale_in_a_full_launch(name):
+    """The rescaling inputs among enough one-token prompts that the 128-column
+    kernel runs them (alone they take the unit-dividing one)."""
+    case, hq, hkv, scale, dtype = softmax_rises.make(name)
+    group, rows = hq // hkv, len(case["q"])
+    n = 512 // (-(-int(np.diff(case["cu_q"]).max()) * group // 32) * hkv) + 1
+    pad = workloads.make_prefill_case([0] * n, [1] * n, hq, hkv, dtype=dtype, seed=213)
+    nb, mb = case["pool"].shape[0], case["block_table"].shape[1]
+    bt = np.zeros((n, mb), dtype=np.int32)
+    bt[:, :2] = pad["block_table"][:, :2] + nb
+    both = dict(case)
+    for k in ("pool", "q", "k_new", "v_new", "seq_lens"):
+        both[k] = np.concatenate([case[k], pad[k]])
+    both["block_table"] = np.concatenate([case["block_table"], bt])
+    both["tags"] = np.zeros_like(both["block_table"], dtype=np.uint8)
+    both["slots"] = np.concatenate([case["slots"], pad["slots"] + nb * 16]).astype(np.int32)
+    both["cu_q"] = np.concatenate([case["cu_q"], rows + pad["cu_q"][1:]]).astype(np.int32)
+    _run(both, hq, hkv, out_fp32=True, scale=scale)
