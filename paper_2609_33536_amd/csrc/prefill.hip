@@ -453,14 +453,15 @@ struct Extent {
 // head)s would load the XCDs unevenly (12 of them: 1.4x the time), and the
 // tiles are spread instead.
 __device__ __forceinline__ void place(const PrefillArgs& a, int tiles, int* grp, int* tile) {
+  const int id = blockIdx.y * gridDim.x + blockIdx.x;   // (two grid dimensions only for the launch's size limits)
   if (a.num_kv_heads % 8 == 0) {
-    const int i = blockIdx.x >> 3;
-    *grp = 8 * (i / tiles) + (blockIdx.x & 7);
+    const int i = id >> 3;
+    *grp = 8 * (i / tiles) + (id & 7);
     *tile = tiles - 1 - i % tiles;
   } else {
     const int groups = a.batch * a.num_kv_heads;
-    *grp = blockIdx.x % groups;
-    *tile = tiles - 1 - blockIdx.x / groups;
+    *grp = id % groups;
+    *tile = tiles - 1 - id / groups;
   }
 }
 
@@ -720,7 +721,7 @@ hipError_t launch_typed(const PrefillArgs& a, bool elastic, hipStream_t st) {
   }
   constexpr int kTileTok = kPfWaves * kPfCols / G;
   const int tiles = (a.max_q_len + kTileTok - 1) / kTileTok;
-  const dim3 grid((unsigned)tiles * a.num_kv_heads * a.batch);
+  const dim3 grid((unsigned)tiles * a.num_kv_heads, a.batch);
   if (elastic) hipLaunchKernelGGL((prefill_kernel<T, G, true, F8>), grid, dim3(64 * kPfWaves), 0, st, a);
   else hipLaunchKernelGGL((prefill_kernel<T, G, false, F8>), grid, dim3(64 * kPfWaves), 0, st, a);
   return hipGetLastError();
