@@ -456,8 +456,8 @@ def main():
                     "new_tokens_per_s": round(PF_SEQS * PF_CHUNK / (pf_ms * 1e-3), 1),
                     "pool_MiB": round(pf_pool_bytes / 2**20, 1),
                     "cache_resident": pf_pool_bytes < 256e6,
-                    "note": "a pool under 256 MB fits the last-level cache; the kernel is bound by instruction "
-                            "issue, not by memory"},
+                    "note": "a pool under 256 MB fits the last-level cache; the kernel is bound by matrix "
+                            "work, not by memory"},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": (traffic["hbm_bytes_per_launch"] if traffic else None),
