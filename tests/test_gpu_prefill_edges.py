@@ -79,3 +79,14 @@ def test_prefill_rescale_in_a_full_launch(name):
     both["slots"] = np.concatenate([case["slots"], pad["slots"] + nb * 16]).astype(np.int32)
     both["cu_q"] = np.concatenate([case["cu_q"], rows + pad["cu_q"][1:]]).astype(np.int32)
     _run(both, hq, hkv, out_fp32=True, scale=scale)
+
+
+@pytest.mark.parametrize("longest", [1010, 1040])
+@pytest.mark.parametrize("dtype", ["bf16", "e5m2"])
+def test_prefill_one_column_tile_over_many_sequences(dtype, longest):
+    """More than 512 workgroups of a few rows each: with a context of 1024 keys
+    or more they take the unit-dividing kernel, below it the other."""
+    prefix = [longest - 8] + [(7 * s) % 90 for s in range(65)]
+    chunk = [8] + [1 + s % 8 for s in range(65)]
+    case = workloads.make_prefill_case(prefix, chunk, 32, 8, dtype=dtype, seed=214, base_fraction=0.5, spare_blocks=2)
+    _run(case, 32, 8)
