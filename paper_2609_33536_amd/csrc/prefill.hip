@@ -145,10 +145,14 @@ __device__ __forceinline__ constexpr uint32_t quarter_offset(int q) { return (q 
 // One direct-to-LDS load: lane l's 16 bytes at base + off go to lds + 16 l.
 // Inline assembly (it writes no register) keeps it out of the compiler's wait
 // insertion, which would wait for every load in flight before each transposing
-// LDS read; the kernels wait with explicit counts.
+// LDS read; the kernels wait with explicit counts.  A base may come straight
+// from v_readlane (PairTable::tile): a scalar register written by a vector
+// instruction needs 5 wait states before a vector memory instruction reads it,
+// which the hardware does not check and the compiler only inserts before its
+// own loads.  The move to m0 and s_nop 3 are those 5 (and m0's own one).
 __device__ __forceinline__ void dma16(uint64_t base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
-               : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+               : "memory", "m0");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {
