@@ -150,10 +150,13 @@ __device__ __forceinline__ constexpr uint32_t quarter_offset(int q) { return (q 
 // instruction needs 5 wait states before a vector memory instruction reads it,
 // which the hardware does not check and the compiler only inserts before its
 // own loads.  The move to m0 and s_nop 3 are those 5 (and m0's own one).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // (m0 is named as clobbered although the compiler never allocates it)
 __device__ __forceinline__ void dma16(uint64_t base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
                : "memory", "m0");
 }
+#pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_loads() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
