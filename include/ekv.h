@@ -162,6 +162,10 @@ ekv_status ekv_lower(const uint8_t* h_tags, const int32_t* h_seq_lens, int32_t b
  * workspace of this size serves every call whose batch needs no more, on any
  * device.  At most
  * 2 * 4096 * G * 520 + 32 KiB bytes.  Returns 0 for unsupported shapes.
+ * A smaller workspace is accepted too while it holds one workgroup per 8 pairs
+ * of blocks: the launch then uses the workgroups that fit, each with more of
+ * the work (small batches run slower; the results differ only in the order of
+ * the sums).
  */
 size_t ekv_decode_workspace_bytes(const ekv_pool* pool, const ekv_batch* batch);
 
@@ -189,8 +193,8 @@ ekv_status ekv_decode_workspace_init(void* ws, size_t ws_bytes, hipStream_t stre
  * uses its boundaries and any other sequence reads its tags.
  *   q    device [batch][num_q_heads][head_dim], pool dtype
  *   out  device [batch][num_q_heads][head_dim], out_dtype = pool dtype or EKV_DTYPE_FP32
- *   ws   device scratch of at least ekv_decode_workspace_bytes() bytes,
- *        16-byte aligned, prepared by ekv_decode_workspace_init (or
+ *   ws   device scratch of ekv_decode_workspace_bytes() bytes (or fewer, see
+ *        there), 16-byte aligned, prepared by ekv_decode_workspace_init (or
  *        zero-filled) before its first use; calls sharing one ws must be
  *        ordered on one stream
  * A sequence of length 0 yields zeros.
@@ -235,8 +239,9 @@ ekv_status ekv_attn_decode_append(const ekv_pool* pool, const ekv_batch* batch, 
  * not run.  All calls on one device share the scratch: calls that may
  * overlap on one device (other streams, other threads) race and must be
  * ordered by the caller.  A batch whose launch needs more than 32 MiB of
- * scratch (2 slots of G partial rows per workgroup, plus 32 KiB) returns
- * EKV_ERR_UNSUPPORTED.  Other arguments and errors as ekv_attn_decode.
+ * scratch (2 slots of G partial rows per workgroup, plus 32 KiB) even with 8
+ * pairs of blocks a workgroup returns EKV_ERR_UNSUPPORTED; one that needs more
+ * only for shorter ranges runs with the workgroups that fit.  Other arguments and errors as ekv_attn_decode.
  */
 ekv_status ekv_attn_decode_noalloc(const ekv_pool* pool, const ekv_batch* batch, const void* q, void* out,
                                    int32_t out_dtype, float scale, hipStream_t stream);

@@ -93,14 +93,14 @@ int max_seq_blocks(const ekv_batch* b) {
 // 15.6 / 19.5; 8-bit pool 4 x 1000-4000 21.8 / 19.0 / 16.9 / 19.1; from ~8192 tokens on the
 // rule gives 8, and from ~1024 ranges of 8 pairs in the batch on every launch
 // fills the chip and the rule has no effect.
-// EKV_MIN_CHUNK overrides.
+// EKV_MIN_CHUNK (forced, 0: unset) overrides.
 constexpr int kMostPairs = 8, kPieces = 32;
-int plan_min_chunk(int np_max) {
-  if (const char* env = getenv("EKV_MIN_CHUNK")) {
-    const int v = atoi(env);
-    if (v > 0) return v;
-  }
-  return std::max(1, std::min(kMostPairs, (np_max + kPieces - 1) / kPieces));
+int forced_min_chunk() {
+  const char* env = getenv("EKV_MIN_CHUNK");
+  return env ? std::max(0, atoi(env)) : 0;
+}
+int plan_min_chunk(int np_max, int forced) {
+  return forced ? forced : std::max(1, std::min(kMostPairs, (np_max + kPieces - 1) / kPieces));
 }
 
 // LDS ring depth of the decode kernel: the deepest ring that still lets 4
@@ -114,51 +114,73 @@ int decode_slots(const ekv_pool* p, int group, bool elastic) {
   return slots;
 }
 
-// Workspace: [merge counters u32, 2 kMaxDecodeGrid | (m, l) f32 | o f32
-// rows], 256-B aligned parts; the last two hold two slots per workgroup of
-// the launch (G rows a slot), the counters two per possible workgroup.
-// The launch grid is the kernel's resident workgroups on the device, or
-// fewer for small work, and never more than kMaxDecodeGrid.  The size a
-// caller allocates (exact = false) takes one pair a workgroup and that cap, so
-// it needs no device, serves every mode of a batch shape, and grows with the
-// batch's work whatever range length a call picks: a workspace made for the
-// largest batch serves every smaller one.  The size a call needs (exact =
-// true) uses the device's own grid, the larger of the native and the elastic
-// kernel's.
-struct DecodePlan {
-  int min_chunk, grid;      // grid of the call's own mode (exact plans)
-  long long pairs_max;
+// Workspace of a launch of `grid` workgroups: [merge counters u32, 2
+// kMaxDecodeGrid | (m, l) f32 | o f32 rows], 256-B aligned parts; the last
+// two hold two slots per workgroup (G rows a slot).  The counters keep one
+// place whatever the grid: a workspace reused by calls whose grids differ
+// (other batch sizes) never finds partial rows of an earlier call where a
+// later call expects zero counters.
+struct DecodeLayout {
   size_t ml_offset, o_offset, total;
 };
+DecodeLayout decode_layout(long long grid, int group) {
+  auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t rows = 2 * (size_t)grid * group;
+  DecodeLayout l;
+  l.ml_offset = align(2 * (size_t)ekv::kMaxDecodeGrid * sizeof(uint32_t));
+  l.o_offset = align(l.ml_offset + rows * 2 * sizeof(float));
+  l.total = l.o_offset + rows * ekv::kHeadDim * sizeof(float);
+  return l;
+}
+// The most workgroups whose layout fits `bytes` (0: none).
+long long grid_that_fits(size_t bytes, int group) {
+  const DecodeLayout none = decode_layout(0, group), one = decode_layout(1, group);
+  if (bytes < one.total) return 0;
+  const size_t per = 2 * (size_t)group * (2 + ekv::kHeadDim) * sizeof(float);
+  long long grid = (long long)((bytes - none.o_offset) / per);
+  while (decode_layout(grid, group).total > bytes) --grid;   // (the alignment of o_offset: one step at most)
+  return grid;
+}
 
-ekv_status plan_decode(const ekv_pool* p, const ekv_batch* b, int group, bool exact, DecodePlan* d) {
-  const int nblk = std::max(1, max_seq_blocks(b));
-  const int np_max = (nblk + 1) / 2;
-  d->min_chunk = plan_min_chunk(np_max);
+// Host part of a decode's plan, without the device.  The launch grid is the
+// kernel's resident workgroups on the device, or fewer for small work or a
+// small workspace, and never more than kMaxDecodeGrid.  The reported size is
+// for one pair a workgroup, up to that cap, so it serves every mode of a batch
+// shape and grows with the batch's work whatever range length a call picks: a
+// workspace made for the largest batch serves every smaller one.  A smaller
+// workspace is taken as long as it holds workgroups of kMostPairs pairs (the
+// reported size while that was every launch's shortest range): the grid is
+// then cut to what fits, and the ranges get longer.
+struct DecodePlan {
+  int min_chunk;                // fewest pairs a workgroup streams
+  long long pairs_max;
+  long long finest, coarsest;   // workgroups the reported and the smallest workspace hold
+};
+
+ekv_status plan_decode(const ekv_pool* p, const ekv_batch* b, DecodePlan* d) {
+  const int np_max = (std::max(1, max_seq_blocks(b)) + 1) / 2;
+  const int forced = forced_min_chunk();
+  d->min_chunk = plan_min_chunk(np_max, forced);
   d->pairs_max = (long long)b->batch * p->num_kv_heads * np_max;
   if (d->pairs_max >= (1LL << 30)) return fail(EKV_ERR_UNSUPPORTED, "batch too large for one decode call");
-  int grids[2] = {0, 0};
+  auto workgroups = [&](long long pairs) {
+    return std::max<long long>(1, std::min<long long>((d->pairs_max + pairs - 1) / pairs, ekv::kMaxDecodeGrid));
+  };
+  d->finest = workgroups(1);
+  d->coarsest = workgroups(forced ? forced : kMostPairs);
+  return EKV_OK;
+}
+
+// The grids of the native and the elastic kernel on the current device.
+ekv_status device_grids(const ekv_pool* p, int group, const DecodePlan& d, int (&grids)[2]) {
   for (int elastic = 0; elastic < 2; ++elastic) {
-    if (!exact) {
-      grids[elastic] = (int)std::max<long long>(1, std::min<long long>(d->pairs_max, ekv::kMaxDecodeGrid));
-      continue;
-    }
     ekv::DecodeArgs a{};
-    a.pairs_max = d->pairs_max;
-    a.min_chunk = d->min_chunk;
+    a.pairs_max = d.pairs_max;
+    a.min_chunk = d.min_chunk;
     a.slots = decode_slots(p, group, elastic != 0);
     const hipError_t e = ekv::decode_grid(a, p->dtype, group, elastic != 0, &grids[elastic]);
     if (e != hipSuccess) return hip_status(e, "decode grid");
   }
-  d->grid = grids[b->mode != EKV_MODE_NATIVE ? 1 : 0];
-  const size_t slots = 2 * (size_t)std::max(grids[0], grids[1]);
-  auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  // The counters keep one place whatever the grid: a workspace reused by
-  // calls whose grids differ (other batch sizes) never finds partial rows
-  // of an earlier call where a later call expects zero counters.
-  d->ml_offset = align(2 * (size_t)ekv::kMaxDecodeGrid * sizeof(uint32_t));
-  d->o_offset = align(d->ml_offset + slots * group * 2 * sizeof(float));
-  d->total = d->o_offset + slots * group * ekv::kHeadDim * sizeof(float);
   return EKV_OK;
 }
 
@@ -302,16 +324,22 @@ ekv_status decode_call(const ekv_pool* pool, const ekv_batch* batch, const void*
     return fail(EKV_ERR_INVALID, "out_dtype must be the query dtype or fp32");
   if (!std::isfinite(scale)) return fail(EKV_ERR_INVALID, "scale must be finite");
   DecodePlan plan{};
-  if (!clear_counters) {   // the caller's workspace: at least ekv_decode_workspace_bytes
-    if ((st = plan_decode(pool, batch, group, false, &plan)) != EKV_OK) return st;
-    if (!ws || ws_bytes < plan.total)
-      return fail(EKV_ERR_INVALID, "workspace of %zu bytes needed, %zu given", plan.total, ws_bytes);
+  if ((st = plan_decode(pool, batch, &plan)) != EKV_OK) return st;
+  const size_t reported = decode_layout(plan.finest, group).total;
+  auto too_small = [&] { return fail(EKV_ERR_INVALID, "workspace of %zu bytes needed, %zu given", reported, ws_bytes); };
+  if (!clear_counters) {   // the caller's workspace
+    if (!ws || ws_bytes < decode_layout(plan.coarsest, group).total) return too_small();
     if (reinterpret_cast<uintptr_t>(ws) % 16)   // the partial rows move in 16-byte accesses
       return fail(EKV_ERR_INVALID, "%s: ws must be 16-byte aligned", who);
   }
-  if ((st = plan_decode(pool, batch, group, true, &plan)) != EKV_OK) return st;
-  if (plan.total > ws_bytes)   // (the static scratch: sized by the device's own grid)
-    return fail(EKV_ERR_UNSUPPORTED, "%s: needs %zu bytes of scratch, %zu available", who, plan.total, ws_bytes);
+  int grids[2] = {0, 0};
+  if ((st = device_grids(pool, group, plan, grids)) != EKV_OK)   // (without a device's grid only the reported size is known to do)
+    return !clear_counters && ws_bytes < reported ? too_small() : st;
+  const size_t least = decode_layout(std::min<long long>(std::max(grids[0], grids[1]), plan.coarsest), group).total;
+  if (least > ws_bytes)   // (the static scratch: sized by the device's own grid)
+    return fail(EKV_ERR_UNSUPPORTED, "%s: needs %zu bytes of scratch, %zu available", who, least, ws_bytes);
+  const int grid = (int)std::min<long long>(grids[batch->mode != EKV_MODE_NATIVE ? 1 : 0], grid_that_fits(ws_bytes, group));
+  const DecodeLayout layout = decode_layout(grid, group);
   // (the debug checks synchronise: not for the no-allocation call)
   if (!clear_counters && debug_mode() && (st = debug_check_batch(pool, batch, stream, who)) != EKV_OK) return st;
   const bool elastic = batch->mode != EKV_MODE_NATIVE;
@@ -323,8 +351,8 @@ ekv_status decode_call(const ekv_pool* pool, const ekv_batch* batch, const void*
   a.tags = batch->tags;
   a.bounds = elastic ? batch->boundaries : nullptr;
   a.counters = static_cast<uint32_t*>(ws);
-  a.ws_ml = reinterpret_cast<float*>(static_cast<char*>(ws) + plan.ml_offset);
-  a.ws_o = reinterpret_cast<float*>(static_cast<char*>(ws) + plan.o_offset);
+  a.ws_ml = reinterpret_cast<float*>(static_cast<char*>(ws) + layout.ml_offset);
+  a.ws_o = reinterpret_cast<float*>(static_cast<char*>(ws) + layout.o_offset);
   a.out = out;
   a.batch = batch->batch;
   a.num_kv_heads = pool->num_kv_heads;
@@ -335,7 +363,7 @@ ekv_status decode_call(const ekv_pool* pool, const ekv_batch* batch, const void*
   if (batch->max_seq_len > 0) a.len_cap = std::min(a.len_cap, batch->max_seq_len);
   a.min_chunk = plan.min_chunk;
   a.pairs_max = plan.pairs_max;
-  a.grid = plan.grid;
+  a.grid = grid;
   a.out_fp32 = out_dtype == EKV_DTYPE_FP32;
   a.slots = decode_slots(pool, group, elastic);
   a.scale_log2 = log2e_scale(scale);
@@ -343,7 +371,7 @@ ekv_status decode_call(const ekv_pool* pool, const ekv_batch* batch, const void*
   a.v_new = v_new;
   a.pool_out = k_new ? pool->kv : nullptr;
   if (clear_counters &&
-      (st = hip_status(ekv::launch_zero_u32(a.counters, 2 * (size_t)plan.grid, stream), "scratch clear")) != EKV_OK)
+      (st = hip_status(ekv::launch_zero_u32(a.counters, 2 * (size_t)grid, stream), "scratch clear")) != EKV_OK)
     return st;
   return hip_status(ekv::launch_decode(a, pool->dtype, group, elastic, stream), "decode launch");
 }
@@ -431,8 +459,8 @@ size_t ekv_decode_workspace_bytes(const ekv_pool* pool, const ekv_batch* batch) 
   int group = 0;   // (no allocation or exception on this path)
   if (check_pool(pool) != EKV_OK || check_attention_batch(pool, batch, &group) != EKV_OK) return 0;
   DecodePlan plan{};
-  if (plan_decode(pool, batch, group, false, &plan) != EKV_OK) return 0;
-  return plan.total;
+  if (plan_decode(pool, batch, &plan) != EKV_OK) return 0;
+  return decode_layout(plan.finest, group).total;
 }
 
 ekv_status ekv_decode_workspace_init(void* ws, size_t ws_bytes, hipStream_t stream) {

@@ -6,6 +6,7 @@
 // device on a CPU-only machine).  Every array is a heap allocation of the
 // exact size the interface documents, so a read or write past it is
 // reported.  Prints "host driver ok" and returns 0 when every call behaved.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -14,6 +15,10 @@
 #include <vector>
 
 #include "ekv.h"
+#include "launch.h"
+
+extern int stub_resident;
+extern ekv::DecodeArgs stub_decode;
 
 namespace {
 
@@ -141,6 +146,56 @@ void controller(std::mt19937& rng) {
   }
 }
 
+// Decode workspaces of every size: the reported size takes the finest
+// ranges; a workspace that holds one workgroup per 8 pairs is taken, with its
+// partial rows inside it; a smaller one is refused.
+void workspaces(std::mt19937& rng) {
+  const int groups[] = {1, 2, 4, 8, 16};
+  int32_t* some = exact<int32_t>(64);
+  for (int k = 0; k < 20000; ++k) {
+    const int group = groups[rng() % 5], hkv = 1 + rng() % 8, rows = 1 + rng() % (k % 2 ? 300 : 6);
+    const int max_blocks = 1 + rng() % (k % 3 ? 40 : 3000);
+    ekv_pool pool{some, 64, hkv, 16, 128, k % 5 ? EKV_DTYPE_BF16 : EKV_DTYPE_E5M2};
+    ekv_batch batch{rows, group * hkv, max_blocks, (int)(rng() % 3), 0, some, some,
+                    reinterpret_cast<const uint8_t*>(some), some};
+    const long long pairs = (long long)rows * hkv * ((max_blocks + 1) / 2);
+    auto bytes = [&](long long grid) {   // counters, (m, l) and rows of 2 slots a workgroup
+      const size_t ml = 2 * (size_t)grid * group * 8;
+      return (size_t)32768 + (ml + 255) / 256 * 256 + 2 * (size_t)grid * group * 512;
+    };
+    const long long coarse = std::max(1LL, std::min(4096LL, (pairs + 7) / 8));
+    const size_t need = ekv_decode_workspace_bytes(&pool, &batch), least = bytes(coarse);
+    expect(need >= least, "reported workspace", k);
+    stub_resident = 1 + rng() % 2048;
+    const size_t sizes[] = {least - 1, least, least + rng() % (need - least + 1), need, need + 1 + rng() % 4096};
+    long long grid[5] = {0};
+    for (int i = 0; i < 5; ++i) {
+      stub_decode = ekv::DecodeArgs{};
+      const ekv_status st = ekv_attn_decode(&pool, &batch, some, some, EKV_DTYPE_FP32, 1.f,
+                                            reinterpret_cast<void*>(uintptr_t(1) << 40), sizes[i], nullptr);
+      if (i == 0) {
+        expect(st == EKV_ERR_INVALID, "workspace below one workgroup per 8 pairs", k);
+        continue;
+      }
+      expect(st == EKV_OK && stub_decode.grid >= 1, "workspace taken", k);
+      if (st != EKV_OK) continue;
+      grid[i] = stub_decode.grid;
+      const size_t base = size_t(1) << 40;
+      const size_t ml = reinterpret_cast<size_t>(stub_decode.ws_ml) - base, o = reinterpret_cast<size_t>(stub_decode.ws_o) - base;
+      const size_t slots = 2 * (size_t)grid[i];
+      expect(ml >= 32768 && ml + slots * group * 8 <= o && o % 16 == 0 && o + slots * group * 512 <= sizes[i],
+             "partial rows inside the workspace", k);
+      const long long resident = std::min(4096, stub_resident * (batch.mode != EKV_MODE_NATIVE ? 2 : 1));
+      const long long finest = std::min(resident, (pairs + stub_decode.min_chunk - 1) / stub_decode.min_chunk);
+      expect(grid[i] >= std::min(resident, coarse) && grid[i] <= finest, "grid", k);
+      if (sizes[i] >= need) expect(grid[i] == finest, "the reported size takes the finest ranges", k);
+      if (i > 1) expect(grid[i] >= grid[i - 1], "more workspace, no fewer workgroups", k);
+    }
+  }
+  stub_resident = 0;
+  std::free(some);
+}
+
 // Argument checks of the device entry points: every call here must return
 // an error before any device work (no device exists on this machine, and
 // the pointers are not device memory).
@@ -198,6 +253,7 @@ int main() {
   lowering(rng);
   transitions(rng);
   controller(rng);
+  workspaces(rng);
   arguments();
   if (failures) {
     std::fprintf(stderr, "%d failures\n", failures);
