@@ -145,15 +145,11 @@ __device__ __forceinline__ constexpr uint32_t quarter_offset(int q) { return (q 
 // One direct-to-LDS load: lane l's 16 bytes at base + off go to lds + 16 l.
 // Inline assembly (it writes no register) keeps it out of the compiler's wait
 // insertion, which would wait for every load in flight before each transposing
-// LDS read; the kernels wait with explicit counts.  A base may come straight
-// from v_readlane (PairTable::tile): a scalar register written by a vector
-// instruction needs 5 wait states before a vector memory instruction reads it,
-// which the hardware does not check and the compiler only inserts before its
-// own loads.  The move to m0 and s_nop 3 are those 5 (and m0's own one).
+// LDS read; the kernels wait with explicit counts.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"   // (m0 is named as clobbered although the compiler never allocates it)
 __device__ __forceinline__ void dma16(uint64_t base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
                : "memory", "m0");
 }
 #pragma clang diagnostic pop
@@ -309,8 +305,15 @@ struct PairTable {
   __device__ __forceinline__ uint64_t tile(int u, int member) const {
     const uint64_t a = member ? addr1 : addr0;
     const int l = u & (kPfWindow - 1);
-    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(a >> 32), l) << 32) |
-           (uint32_t)__builtin_amdgcn_readlane((uint32_t)a, l);
+    uint64_t at = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(a >> 32), l) << 32) |
+                  (uint32_t)__builtin_amdgcn_readlane((uint32_t)a, l);
+    // A scalar register that a vector instruction writes needs 5 wait states
+    // before a vector memory instruction reads it; the hardware does not check,
+    // and the compiler does not look into dma16.  These 3, and the 2 before
+    // dma16's load, for all the loads that use the address (waiting in every
+    // load cost the 8B chunked prefill 1 %).
+    asm("s_nop 2" : "+s"(at));
+    return at;
   }
 };
 
