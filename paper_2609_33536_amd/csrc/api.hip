@@ -531,7 +531,7 @@ ekv_status ekv_attn_prefill(const ekv_pool* pool, const ekv_batch* batch, const 
     a.num_kv_heads = pool->num_kv_heads;
     a.num_q_heads = batch->num_q_heads;
     a.max_blocks = batch->max_blocks;
-    a.max_q_len = max_q_len;
+    a.max_q_len = std::min(max_q_len, total_q);   // (no sequence has more rows; the caller's bound may be loose)
     a.num_blocks = pool->num_blocks;
     a.total_q = total_q;
     a.max_len = max_seq_blocks(batch) * ekv::kPage;

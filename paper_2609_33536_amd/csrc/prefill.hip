@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "attn_device.h"
+#include "prefill_plan.h"
 
 namespace ekv {
 namespace {
@@ -456,23 +457,8 @@ struct Extent {
   __device__ __forceinline__ int seen(int t) const { return max(1, min(len, len - nq + t + 1)); }
 };
 
-// Workgroup -> (sequence, KV head), query tile; the last tiles (most keys)
-// first.  Ids go round robin over the 8 XCDs: with a multiple of 8 KV heads
-// all tiles of one (sequence, KV head) go to one XCD and share its L2, and
-// every XCD gets a KV head of every sequence; otherwise whole (sequence, KV
-// head)s would load the XCDs unevenly (12 of them: 1.4x the time), and the
-// tiles are spread instead.
-__device__ __forceinline__ void place(const PrefillArgs& a, int tiles, int* grp, int* tile) {
-  const int id = blockIdx.y * gridDim.x + blockIdx.x;   // (two grid dimensions only for the launch's size limits)
-  if (a.num_kv_heads % 8 == 0) {
-    const int i = id >> 3;
-    *grp = 8 * (i / tiles) + (id & 7);
-    *tile = tiles - 1 - i % tiles;
-  } else {
-    const int groups = a.batch * a.num_kv_heads;
-    *grp = id % groups;
-    *tile = tiles - 1 - id / groups;
-  }
+__device__ __forceinline__ PrefillPlace place(const PrefillArgs& a, int tiles) {
+  return place_workgroup(blockIdx.x, blockIdx.y, gridDim.x, gridDim.y, tiles, a.num_kv_heads, a.batch);
 }
 
 // ---- 4 waves x 32 columns over shared units --------------------------------
@@ -502,9 +488,8 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
   __shared__ __attribute__((aligned(16))) char ring[kPfRing * kSlotPf];
   constexpr int kTileTok = kPfWaves * kPfCols / G;
   const int tiles = (a.max_q_len + kTileTok - 1) / kTileTok;
-  int grp, tile;
-  place(a, tiles, &grp, &tile);
-  const int s = grp / a.num_kv_heads, kvh = grp % a.num_kv_heads;
+  const PrefillPlace at = place(a, tiles);
+  const int s = at.seq, kvh = at.kv_head, tile = at.tile;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, h = lane >> 5;
   const Extent x(a, s);
@@ -613,9 +598,8 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(1
   __shared__ __attribute__((aligned(16))) char ring[kPfWaves * 2 * kSlotPf];
   constexpr int kTileTok = kPfCols / G;
   const int tiles = (a.max_q_len + kTileTok - 1) / kTileTok;
-  int grp, tile;
-  place(a, tiles, &grp, &tile);
-  const int s = grp / a.num_kv_heads, kvh = grp % a.num_kv_heads;
+  const PrefillPlace at = place(a, tiles);
+  const int s = at.seq, kvh = at.kv_head, tile = at.tile;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, h = lane >> 5;
   const Extent x(a, s);

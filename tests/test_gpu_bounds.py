@@ -109,3 +109,25 @@ def test_prefill_clamps_query_offsets_to_total_q():
     ref = oatt.prefill(c["q"], c["cu_q"], otr.append(c["pool"], c["slots"], c["k_new"], c["v_new"]),
                        c["block_table"], c["tags"], c["seq_lens"])
     check_attention(got[:total], ref, True)
+
+
+@pytest.mark.parametrize("hint", [21, 1000, 1 << 24, (1 << 31) - 1])
+def test_prefill_with_a_loose_bound_on_the_chunks(hint):
+    """max_q_len is only an upper bound: any value above the longest chunk works."""
+    torch = require_gpu()
+    hq, hkv = 8, 2
+    c = workloads.make_prefill_case([64, 32, 500], [20, 10, 3], hq, hkv, seed=83, base_fraction=0.5, spare_blocks=2)
+    host_safety_check(c, c["pool"].shape)
+    kv = kvpool.PagedKV(c["pool"], c["block_table"], c["seq_lens"], c["free"], hkv)
+    kv.append(torch.from_numpy(c["slots"]).cuda(), words_to_tensor(c["k_new"], torch, "bf16"),
+              words_to_tensor(c["v_new"], torch, "bf16"))
+    kv.demote(c["pairs"])
+    kv.relower()
+    q = words_to_tensor(c["q"], torch, "bf16")
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    print(f"prefill with max_q_len {hint}", flush=True)
+    ekv.attn_prefill(kv.pool, kv.batch(hq), q, torch.from_numpy(c["cu_q"]).cuda(), hint, out, default_scale())
+    torch.cuda.synchronize()
+    pool, bt, tags, _, _ = otr.demote(otr.append(c["pool"], c["slots"], c["k_new"], c["v_new"]), c["block_table"],
+                                      c["tags"], c["pairs"], c["seq_lens"])
+    check_attention(out.cpu().numpy(), oatt.prefill(c["q"], c["cu_q"], pool, bt, tags, c["seq_lens"]), True)

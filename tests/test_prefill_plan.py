@@ -1,0 +1,61 @@
+"""The prefill launch's host-checkable parts (csrc/prefill_plan.h), built with
+the host compiler: every grid is covered exactly once, also one whose
+workgroups have no 31-bit id."""
+
+import ctypes
+import itertools
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2609_33536_amd import build
+
+SOURCE = """
+#include "prefill_plan.h"
+extern "C" void place(uint32_t bx, uint32_t by, uint32_t gx, uint32_t gy, int tiles, int hkv, int batch, int* out) {
+  const ekv::PrefillPlace p = ekv::place_workgroup(bx, by, gx, gy, tiles, hkv, batch);
+  out[0] = p.seq, out[1] = p.kv_head, out[2] = p.tile;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("g++ or the HIP headers missing")
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(SOURCE)
+    p = subprocess.run([gxx, "-O1", "-std=c++17", "-shared", "-fPIC", "-ftrapv", "-D__HIP_PLATFORM_AMD__",
+                        "-I/opt/rocm/include", f"-I{build.CSRC}", "plan.cpp", "-o", "plan.so"], cwd=d,
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert p.returncode == 0, p.stdout[-3000:]
+    return ctypes.CDLL(str(d / "plan.so"))
+
+
+def _place(plan, bx, by, gx, gy, tiles, hkv, batch):
+    out = (ctypes.c_int * 3)()
+    plan.place(bx, by, gx, gy, tiles, hkv, batch, out)
+    return tuple(out)
+
+
+@pytest.mark.parametrize("tiles,hkv,batch", itertools.product([1, 2, 7], [1, 2, 3, 8, 16], [1, 3, 16]))
+def test_every_tile_once(plan, tiles, hkv, batch):
+    gx, gy = tiles * hkv, batch
+    got = {_place(plan, bx, by, gx, gy, tiles, hkv, batch) for by in range(gy) for bx in range(gx)}
+    assert got == set(itertools.product(range(batch), range(hkv), range(tiles)))
+
+
+@pytest.mark.parametrize("tiles,hkv,batch", [(16384, 8, 16384), (1 << 18, 8, 65535), (1 << 21, 3, 65535)])
+def test_grids_beyond_31_bits(plan, tiles, hkv, batch):
+    gx, gy = tiles * hkv, batch
+    assert gx * gy >= 1 << 31 and gx * 256 < 1 << 32
+    seen = set()
+    for by in (0, 1, batch // 2, batch - 1):
+        for bx in (0, 1, hkv - 1, hkv, gx // 2, gx - hkv, gx - 1):
+            s, h, t = _place(plan, bx, by, gx, gy, tiles, hkv, batch)
+            assert s == by and (h, t) == (bx % hkv, tiles - 1 - bx // hkv) and 0 <= t < tiles
+            seen.add((s, h, t))
+    assert len(seen) == 4 * len({0, 1, hkv - 1, hkv, gx // 2, gx - hkv, gx - 1})
