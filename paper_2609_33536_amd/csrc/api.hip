@@ -535,6 +535,7 @@ ekv_status ekv_attn_prefill(const ekv_pool* pool, const ekv_batch* batch, const 
     a.num_blocks = pool->num_blocks;
     a.total_q = total_q;
     a.max_len = max_seq_blocks(batch) * ekv::kPage;
+    a.len_stated = batch->max_seq_len > 0;
     a.out_fp32 = out_dtype == EKV_DTYPE_FP32;
     a.scale_log2 = log2e_scale(scale);
     return hip_status(ekv::launch_prefill(a, pool->dtype, group, batch->mode != EKV_MODE_NATIVE, stream),

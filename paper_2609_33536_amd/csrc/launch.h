@@ -105,7 +105,8 @@ struct PrefillArgs {
   int32_t batch, num_kv_heads, num_q_heads, max_blocks, max_q_len, out_fp32;
   int32_t num_blocks;        // pool size: table entries are clamped into it
   int32_t total_q;           // rows of q and out: query offsets are clamped into them
-  int32_t max_len;           // upper bound on seq_lens[] (chooses the kernel)
+  int32_t max_len;           // upper bound on seq_lens[] (chooses the kernel):
+  int32_t len_stated;        //   the caller's own (else the table's width)
   float scale_log2;
 };
 

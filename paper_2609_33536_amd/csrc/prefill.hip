@@ -33,6 +33,7 @@
 //   prefill_kernel        4 waves x 32 columns share every unit;
 //   prefill_split_kernel  4 waves share 32 columns and take every fourth unit
 //                         each: small launches, which leave most CUs idle.
+#include <cstdlib>
 #include <type_traits>
 
 #include "attn_device.h"
@@ -690,29 +691,13 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(1
   if (col.ok) store_tile<T>(a, col.row, o, 1.0f / sum, wave, h);
 }
 
-// Whether a launch that would have `workgroups` workgroups of 32 columns uses
-// prefill_split_kernel: if they fit the 256 CUs at once (one a CU), or
-// twice that over contexts of at least 512 keys, where a quarter of the chain
-// saves more than the second round's start and merge cost.  Measured (us with
-// the append, 128-column / split kernel): 8 workgroups, 4715 + 3 keys 92 / 43;
-// 208, 4322 + 412 139 / 69; 240, 7368 + 18 173 / 75; 384, 3750 + 61 78 / 54; 408, 700 + 130
-// 28.8 / 17.2; beyond the line 320, 182 + 45 16.7 / 18.9; 720, 523 + 236 31.4 / 36.6;
-// 1088, 539 20.6 / 24.0; 16384 (the 8B chunked prefill) 481 / 948.
-// Chunks of one 32-column tile leave three of prefill_kernel's waves without
-// columns whatever the number of workgroups; over contexts of at least 1024
-// keys they always divide the units (560 workgroups, 3500 + 5 184 / 145; 800, 2000 + 8 114 /
-// 95; 2048, 4096 + 4 452 / 419; 1600, 1100 + 8 132 / 128; below the line 1600, 760 + 8 110 / 116).
-constexpr int kChipCus = 256;
-bool divide_units(int64_t workgroups, int64_t columns, int max_len) {
-  return workgroups <= kChipCus || (workgroups <= 2 * kChipCus && max_len >= 512) ||
-         (columns <= kPfCols && max_len >= 1024);
-}
-
 template <typename T, int G, bool F8>
 hipError_t launch_typed(const PrefillArgs& a, bool elastic, hipStream_t st) {
   constexpr int kSplitTok = kPfCols / G;
   const int64_t split = (int64_t)((a.max_q_len + kSplitTok - 1) / kSplitTok) * a.num_kv_heads * a.batch;
-  if (divide_units(split, (int64_t)a.max_q_len * G, a.max_len)) {
+  // (EKV_PREFILL_SPLIT = 0 or 1 overrides, for tests and measurements)
+  const char* forced = getenv("EKV_PREFILL_SPLIT");
+  if (forced ? atoi(forced) != 0 : divide_units(split, (int64_t)a.max_q_len * G, a.max_len, a.len_stated != 0)) {
     const dim3 grid((unsigned)(split / a.batch), a.batch);
     if (elastic) hipLaunchKernelGGL((prefill_split_kernel<T, G, true, F8>), grid, dim3(64 * kPfWaves), 0, st, a);
     else hipLaunchKernelGGL((prefill_split_kernel<T, G, false, F8>), grid, dim3(64 * kPfWaves), 0, st, a);

@@ -1,11 +1,38 @@
 // Parts of the prefill launch that also compile for the host (internal
-// header): which work a workgroup of the grid takes.
+// header): which kernel a launch uses, and which work a workgroup takes.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace ekv {
+
+// Whether a launch that would have `workgroups` workgroups of 32 columns uses
+// prefill_split_kernel (`columns`: the longest chunk's; max_len: the context
+// bound, stated by the caller or the table's width).  Measured (us, bf16, half
+// BASE, 128-column / split kernel):
+//  - up to 256 workgroups (one a CU): always.  128 workgroups of 8 rows over
+//    16-215 keys 12.9 / 10.1, over 4096 112 / 57;
+//  - up to 512 over contexts of at least 512 keys, where a quarter of the chain
+//    saves more than the second round's start and merge cost: 384 and 512
+//    workgroups with one context of 4096 among short ones 112 / 53 and 113 / 54,
+//    three chunks of 130 rows over 2000 keys 68 / 59; all contexts alike 384
+//    x 1100 42 / 43, 512 x 1100 43 / 48; short ones 512 x 16-215 16.1 / 19.1;
+//  - chunks of one 32-column tile leave three of prefill_kernel's waves without
+//    columns whatever the number of workgroups: up to 2048 over contexts of at
+//    least 1024 keys.  One context of 4096 among short ones at 528 / 1024 / 2048
+//    workgroups 114 / 55, 115 / 56, 116 / 68; all of 2000 keys 127 / 106, 152 /
+//    157, 298 / 300.  Beyond, the split kernel's single workgroup a CU costs
+//    more: one long context at 4096 and 8192 workgroups 119 / 135, 209 / 266
+//    (all of 4096 keys 1126 / 1088, 2230 / 2154).  And only if the caller states
+//    the bound: the table's width says nothing about the lengths, and all-short
+//    batches lose (16-215 keys at 528 / 1024 / 2048 workgroups 20.4 / 22.7, 28.5 /
+//    33.9, 49 / 64).
+inline bool divide_units(int64_t workgroups, int64_t columns, int max_len, bool stated) {
+  constexpr int64_t kCus = 256;
+  return workgroups <= kCus || (workgroups <= 2 * kCus && max_len >= 512) ||
+         (workgroups <= 8 * kCus && columns <= 32 && stated && max_len >= 1024);
+}
 
 struct PrefillPlace {
   int seq, kv_head, tile;

@@ -17,10 +17,12 @@ def _run(case, hq, hkv, **kw):
         test_gpu_prefill._run_prefill(case, hq, hkv, **kw)
 
 
-def _routed(prefix, chunk, group, hkv, split):
-    """The sequences in batches of one kernel: for the unit-dividing one, as many
-    as keep its 32-column workgroups within 256; for the other, all of them and
-    one-token prompts until there are more than 512."""
+def _routed(prefix, chunk, group, hkv, split, monkeypatch):
+    """The sequences in batches as each kernel gets them: for the unit-dividing
+    one, as many as keep its 32-column workgroups within 256; for the other, all
+    of them and one-token prompts until there are more than 512.  The kernel is
+    forced, so that a change of the rule does not change what is tested."""
+    monkeypatch.setenv("EKV_PREFILL_SPLIT", "1" if split else "0")
     tiles = -(-max(chunk) * group // 32)
     if split:
         per = max(1, 256 // (tiles * hkv))
@@ -30,40 +32,43 @@ def _routed(prefix, chunk, group, hkv, split):
 
 
 @pytest.mark.parametrize("split", [True, False])
+@pytest.mark.parametrize("fraction", [0.0, 0.6])
 @pytest.mark.parametrize("dtype", ["bf16", "fp16", "e5m2"])
 @pytest.mark.parametrize("group,hkv", [(4, 8), (16, 3), (1, 2)])
-def test_prefill_tile_unit_and_ring_edges(group, hkv, dtype, split):
+def test_prefill_tile_unit_and_ring_edges(group, hkv, dtype, fraction, split, monkeypatch):
     """Chunks one row below, at and above a query tile (128 / group tokens) and
     a wave's columns; contexts of 1 .. 6 units (32 keys) and one key around a
     unit, with whole, lone and partly filled last blocks, and waves without a
-    unit or with only masked ones; BASE and TARGET units mixed.  8 KV heads take
+    unit or with only masked ones; BASE and TARGET units mixed, or TARGET only
+    (the native kernels).  8 KV heads take
     the one-XCD-per-head order of the workgroups, 3 and 2 the other."""
     tile = 128 // group
     prefix = [0, 0, 0, 1, 15, 16, 31, 32, 33, 47, 64, 96, 128, 160]
     chunk = [1, tile, tile + 1, tile - 1 or 1, 1, 16, 1, 2, 31, 1, 32, tile, 33, 1]
-    for k, (p, c) in enumerate(_routed(prefix, chunk, group, hkv, split)):
-        case = workloads.make_prefill_case(p, c, group * hkv, hkv, dtype=dtype, seed=211 + k, base_fraction=0.6,
-                                           spare_blocks=2)
+    for k, (p, c) in enumerate(_routed(prefix, chunk, group, hkv, split, monkeypatch)):
+        case = workloads.make_prefill_case(p, c, group * hkv, hkv, dtype=dtype, seed=211 + k,
+                                           base_fraction=fraction, spare_blocks=2)
         _run(case, group * hkv, hkv)
 
 
 @pytest.mark.parametrize("split", [True, False])
 @pytest.mark.parametrize("dtype", ["bf16", "e5m2"])
-@pytest.mark.parametrize("placement", ["random", "oldest"])
-def test_prefill_metadata_window_edges(placement, dtype, split):
+@pytest.mark.parametrize("placement,fraction", [("random", 0.5), ("oldest", 0.5), ("random", 0.0)])
+def test_prefill_metadata_window_edges(placement, fraction, dtype, split, monkeypatch):
     """Contexts that end one block before, at and after the 64-pair (2048-token)
     windows of the block table."""
-    for p, c in _routed([2016, 2030, 2048, 2049, 4095], [16, 18, 1, 31, 2], 4, 2, split):
-        case = workloads.make_prefill_case(p, c, 8, 2, dtype=dtype, seed=212, base_fraction=0.5, placement=placement,
-                                           spare_blocks=2)
+    for p, c in _routed([2016, 2030, 2048, 2049, 4095], [16, 18, 1, 31, 2], 4, 2, split, monkeypatch):
+        case = workloads.make_prefill_case(p, c, 8, 2, dtype=dtype, seed=212, base_fraction=fraction,
+                                           placement=placement, spare_blocks=2)
         _run(case, 8, 2)
         _run(case, 8, 2, use_boundaries=False)
 
 
 @pytest.mark.parametrize("name", ["aligned-bf16", "scale1-bf16-g16", "aligned-e5m2"])
-def test_prefill_rescale_in_a_full_launch(name):
+def test_prefill_rescale_in_a_full_launch(name, monkeypatch):
     """The rescaling inputs among enough one-token prompts that the 128-column
     kernel runs them (alone they take the unit-dividing one)."""
+    monkeypatch.setenv("EKV_PREFILL_SPLIT", "0")
     case, hq, hkv, scale, dtype = softmax_rises.make(name)
     group, rows = hq // hkv, len(case["q"])
     n = 512 // (-(-int(np.diff(case["cu_q"]).max()) * group // 32) * hkv) + 1

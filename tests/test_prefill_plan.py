@@ -1,6 +1,6 @@
 """The prefill launch's host-checkable parts (csrc/prefill_plan.h), built with
 the host compiler: every grid is covered exactly once, also one whose
-workgroups have no 31-bit id."""
+workgroups have no 31-bit id; and the choice of the kernel at its lines."""
 
 import ctypes
 import itertools
@@ -17,6 +17,9 @@ SOURCE = """
 extern "C" void place(uint32_t bx, uint32_t by, uint32_t gx, uint32_t gy, int tiles, int hkv, int batch, int* out) {
   const ekv::PrefillPlace p = ekv::place_workgroup(bx, by, gx, gy, tiles, hkv, batch);
   out[0] = p.seq, out[1] = p.kv_head, out[2] = p.tile;
+}
+extern "C" int divides(int64_t workgroups, int64_t columns, int max_len, int stated) {
+  return ekv::divide_units(workgroups, columns, max_len, stated != 0);
 }
 """
 
@@ -59,3 +62,15 @@ def test_grids_beyond_31_bits(plan, tiles, hkv, batch):
             assert s == by and (h, t) == (bx % hkv, tiles - 1 - bx // hkv) and 0 <= t < tiles
             seen.add((s, h, t))
     assert len(seen) == 4 * len({0, 1, hkv - 1, hkv, gx // 2, gx - hkv, gx - 1})
+
+
+@pytest.mark.parametrize("workgroups,columns,max_len,stated,split", [
+    (1, 4096, 16, False, True), (256, 4096, 16, False, True),                       # they fit the chip at once
+    (257, 64, 511, True, False), (257, 64, 512, False, True), (512, 64, 512, True, True), (513, 64, 8192, True, False),
+    (513, 32, 1024, True, True), (2048, 32, 8192, True, True), (2049, 32, 8192, True, False),
+    (513, 32, 1023, True, False), (513, 33, 8192, True, False),
+    (513, 32, 8192, False, False), (4096, 32, 8192, False, False),                  # only the table's width: no claim
+    (1 << 40, 1 << 30, 1 << 30, True, False)])
+def test_choice_of_the_kernel(plan, workgroups, columns, max_len, stated, split):
+    plan.divides.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    assert bool(plan.divides(workgroups, columns, max_len, stated)) == split
