@@ -284,8 +284,10 @@ ekv_status ekv_append_kv(const ekv_pool* pool, const int32_t* slots, const void*
  * memory, another device's memory, memory the runtime cannot describe --
  * is EKV_ERR_INVALID with nothing enqueued); then
  * block_table[s][2j+1] = b0, both tags = BASE and freed_out[i] = b1 (device
- * int32 [n]).  b1's bytes are not touched.  The caller returns freed_out[]
- * to its free pool only after the stream has passed this call.
+ * int32 [n]).  b1's bytes are not touched.  The data, the table entry, the
+ * tags and freed_out[i] are written in no particular order within the call:
+ * the caller reads them, and returns freed_out[] to its free pool, only after
+ * the stream has passed this call.
  * Errors: EKV_ERR_INVALID, EKV_ERR_UNSUPPORTED, EKV_ERR_HIP, EKV_ERR_HOST.
  */
 ekv_status ekv_demote(const ekv_pool* pool, int32_t n, const int32_t* pairs,
@@ -387,7 +389,9 @@ ekv_status ekv_promote_publish(const ekv_pool* pool, int32_t n, const int32_t* p
  * batch costs 25.44 ms per invocation (App. C.6), while its traffic is
  * 4 block-equivalents per pair per layer.  Per layer l the data change is
  * exactly that of ekv_demote / ekv_refine on pool layer_kv[l]; the block
- * table, tags and freed list are updated once, after every layer's data.
+ * table, tags and freed list are updated once.  Within the call the updates
+ * and the layers' data are written in no particular order; all of it is done
+ * when the stream has passed the call.
  *   pool      shape and dtype shared by every layer (pool->kv must be non-NULL
  *             -- e.g. layer 0's pool -- but is not read)
  *   layer_kv  device uint64 [num_layers]: the address of each layer's pool
