@@ -11,14 +11,10 @@
 // same bytes, which is what makes the in-place rewrite race-free.
 //
 // The block-table and tag updates of a pair are made by the workgroup of its
-// last tile (of the last layer), in the same launch: a second commit kernel
-// cost a launch and its gap (16 pairs demoted and refined back, host calls
-// included: 22.6 us with them, 16.8 us without).  The other tiles
-// of the pair may read the table before or after that update.  A refinement only
-// checks the entry that changes, and both its values pass or fail together.  A
-// demotion recognises the updated entry (it equals member 0's, which no TARGET
-// pair's does) and takes member 1's block from freed[i], which is written
-// through to memory before the entry is.
+// last tile (of the last layer), in the same launch (pair_commit.h: how the
+// pair's other tiles stay right whether they read the table before or after):
+// a second commit kernel cost a launch and its gap (16 pairs demoted and refined
+// back, host calls included: 22.6 us with them, 16.8 us without).
 //
 // A staged refinement finds a pair's refinement bytes in its new block Q,
 // where an asynchronous host-to-device copy put them while the pair stayed
@@ -37,6 +33,7 @@
 // waves and committed once.
 #include "common.h"
 #include "launch.h"
+#include "pair_commit.h"
 
 namespace ekv {
 namespace {
@@ -67,42 +64,59 @@ __device__ __forceinline__ size_t lo_offset(const TransitionArgs& a, int i, size
 __device__ __forceinline__ bool pair_ok(const TransitionArgs& a, int s, int j) {
   return (unsigned)s < (unsigned)a.batch && j >= 0 && 2 * j + 1 < a.max_blocks;
 }
-__device__ __forceinline__ bool block_ok(const TransitionArgs& a, int b) { return (unsigned)b < (unsigned)a.num_blocks; }
-// the pair's two table entries, or false (the second one is read past the
-// caches: another workgroup of this launch may update it)
-__device__ __forceinline__ bool pair_blocks(const TransitionArgs& a, int s, int j, int& b0, int& b1) {
-  if (!pair_ok(a, s, j)) return false;
-  const int32_t* row = a.bt + (size_t)s * a.max_blocks;
-  b0 = row[2 * j];
-  b1 = __hip_atomic_load(row + 2 * j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return block_ok(a, b0) && block_ok(a, b1);
-}
 
 // The workgroup that updates the table for its pair.
 __device__ __forceinline__ bool commits(const TransitionArgs& a) {
   return blockIdx.x == gridDim.x - 1 && (int)blockIdx.z == a.num_layers - 1;
 }
 
-// Demotion of list entry i = pair (s, j): the pair's blocks, or false (a
-// skipped entry: nothing is freed).  The committing workgroup writes freed[i].
-__device__ __forceinline__ bool demote_blocks(const TransitionArgs& a, int i, int s, int j, int& b0, int& b1) {
-  const bool ok = pair_blocks(a, s, j, b0, b1);
-  int32_t* freed = a.freed + i;
-  if (commits(a)) {
-    if (threadIdx.x == 0) __hip_atomic_store(freed, ok ? b1 : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } else if (ok && b1 == b0) {   // already updated
-    b1 = __hip_atomic_load(freed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return block_ok(a, b1);
+// The second table entry of a pair and its list entry's freed block, read and
+// written past the caches: another workgroup of this launch may do so too.
+struct PairCells {
+  int32_t *entry, *freed;
+  __device__ __forceinline__ PairCells(const TransitionArgs& a, int i, int s, int j)
+      : entry(a.bt + (size_t)s * a.max_blocks + 2 * j + 1), freed(a.freed + i) {}
+  static __device__ __forceinline__ int load(const int32_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  return ok;
+  static __device__ __forceinline__ void store(int32_t* p, int v) {
+    if (threadIdx.x == 0) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ int load_entry() const { return load(entry); }
+  __device__ __forceinline__ int load_freed() const { return load(freed); }
+  __device__ __forceinline__ void store_entry(int v) const { store(entry, v); }
+  __device__ __forceinline__ void store_freed(int v) const { store(freed, v); }
+};
+
+// Demotion of list entry i = pair (s, j): the pair's blocks, or false (a
+// skipped entry).
+__device__ __forceinline__ bool demote_blocks(const TransitionArgs& a, int i, int s, int j, int& b0, int& b1) {
+  if (!pair_ok(a, s, j)) {
+    if (commits(a)) PairCells::store(a.freed + i, -1);
+    return false;
+  }
+  b0 = a.bt[(size_t)s * a.max_blocks + 2 * j];
+  PairCells cells(a, i, s, j);
+  return demotion_block(cells, commits(a), b0, a.num_blocks, b1);
+}
+
+// Refinement of list entry i = pair (s, j): the packed and the new block, or
+// false (a skipped entry).
+__device__ __forceinline__ bool refine_blocks(const TransitionArgs& a, int i, int s, int j, int& bp, int& bq) {
+  if (!pair_ok(a, s, j)) return false;
+  bp = a.bt[(size_t)s * a.max_blocks + 2 * j];
+  bq = a.new_blocks[i];
+  PairCells cells(a, i, s, j);
+  return refinement_ok(cells, bp, bq, a.num_blocks);
 }
 
 // The pair's new table entry and tags, by the committing workgroup once its
 // own loads are in (wait_all_loads: a demotion's freed[i] is then in memory
 // too, before the entry that other tiles recognise changes).
-__device__ __forceinline__ void commit_pair(const TransitionArgs& a, int s, int j, int entry, uint8_t tag) {
-  if (!commits(a) || threadIdx.x != 0) return;
-  __hip_atomic_store(a.bt + (size_t)s * a.max_blocks + 2 * j + 1, entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void commit_pair(const TransitionArgs& a, int i, int s, int j, int entry, uint8_t tag) {
+  if (!commits(a)) return;
+  PairCells(a, i, s, j).store_entry(entry);
+  if (threadIdx.x != 0) return;
   uint8_t* tg = a.tags + (size_t)s * a.max_blocks + 2 * j;
   tg[0] = tag;
   tg[1] = tag;
@@ -127,7 +141,7 @@ __global__ __launch_bounds__(64) void demote_kernel(TransitionArgs a) {
     w1[r] = *reinterpret_cast<const u32x4*>(t1 + 8 * lane + 512 * r);
   }
   wait_all_loads();
-  commit_pair(a, s, j, b0, 1);
+  commit_pair(a, i, s, j, b0, 1);
   uint8_t* packed = reinterpret_cast<uint8_t*>(t0);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -151,9 +165,8 @@ __global__ __launch_bounds__(64) void refine_kernel(TransitionArgs a) {
   const int i = blockIdx.y;
   const int lane = threadIdx.x;
   const int s = a.pairs[2 * i], j = a.pairs[2 * i + 1];
-  int bp = 0, b1 = 0;
-  const int bq = a.new_blocks[i];
-  if (!pair_blocks(a, s, j, bp, b1) || !block_ok(a, bq)) return;
+  int bp = 0, bq = 0;
+  if (!refine_blocks(a, i, s, j, bp, bq)) return;
   const size_t block_words = (size_t)2 * a.num_kv_heads * kTileWords;
   uint16_t* pool = layer_pool(a);
   uint16_t* tp = pool + (size_t)bp * block_words + (size_t)tile * kTileWords;
@@ -174,7 +187,7 @@ __global__ __launch_bounds__(64) void refine_kernel(TransitionArgs a) {
     l1[r] = *reinterpret_cast<const u32x2*>(lo + kTileBytes / 2 + off);
   }
   wait_all_loads();
-  commit_pair(a, s, j, bq, 0);
+  commit_pair(a, i, s, j, bq, 0);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int off = 8 * lane + 512 * r;
@@ -238,7 +251,7 @@ __global__ __launch_bounds__(64) void demote8_kernel(TransitionArgs a) {
     x1[r] = *reinterpret_cast<const u32x4*>(t1 + 32 * lane + 16 * r);
   }
   wait_all_loads();
-  commit_pair(a, s, j, b0, 1);
+  commit_pair(a, i, s, j, b0, 1);
   *reinterpret_cast<u32x4*>(t0 + 16 * lane) = pack_nibbles(x0, true);
   *reinterpret_cast<u32x4*>(t0 + kTile8 / 2 + 16 * lane) = pack_nibbles(x1, true);
   if (a.lo) {
@@ -253,9 +266,8 @@ __global__ __launch_bounds__(64) void refine8_kernel(TransitionArgs a) {
   const int i = blockIdx.y;
   const int lane = threadIdx.x;
   const int s = a.pairs[2 * i], j = a.pairs[2 * i + 1];
-  int bp = 0, b1 = 0;
-  const int bq = a.new_blocks[i];
-  if (!pair_blocks(a, s, j, bp, b1) || !block_ok(a, bq)) return;
+  int bp = 0, bq = 0;
+  if (!refine_blocks(a, i, s, j, bp, bq)) return;
   const size_t block_bytes = (size_t)2 * a.num_kv_heads * kTile8;
   uint8_t* pool = layer_pool8(a);
   uint8_t* tp = pool + (size_t)bp * block_bytes + (size_t)tile * kTile8;
@@ -268,7 +280,7 @@ __global__ __launch_bounds__(64) void refine8_kernel(TransitionArgs a) {
     l[m] = *reinterpret_cast<const u32x4*>(lo + m * (kTile8 / 2) + 16 * lane);
   }
   wait_all_loads();
-  commit_pair(a, s, j, bq, 0);
+  commit_pair(a, i, s, j, bq, 0);
 #pragma unroll
   for (int m = 0; m < 2; ++m) {
     uint8_t* dst = m ? tq : tp;

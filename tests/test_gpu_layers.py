@@ -83,9 +83,10 @@ def test_layers_argument_errors():
     assert np.array_equal(dev.cpu().numpy().view(np.uint16), case["pool"])   # nothing was enqueued
 
 
-@pytest.mark.parametrize("num_layers,hkv", [(33, 1), (24, 8)])
+@pytest.mark.parametrize("num_layers,hkv", [(33, 1), (24, 8), (140, 1)])
 def test_commit_beside_data_over_many_waves(num_layers, hkv):
-    """The table updates are made in the data launch: 2 tiles a layer, and more
-    workgroups than the chip holds at once (so that tiles run before and after
-    the update of their pair)."""
+    """The table updates are made in the data launch, by each pair's last tile:
+    2 tiles a layer, and (the last two) more one-wave workgroups than the chip
+    holds at once, 8192.  The other tiles of a pair nearly always read the table
+    before its update; test_pair_commit.py covers the reads after it."""
     test_demote_refine_all_layers(num_layers, hkv)
