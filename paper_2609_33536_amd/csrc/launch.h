@@ -107,6 +107,7 @@ struct PrefillArgs {
   int32_t total_q;           // rows of q and out: query offsets are clamped into them
   int32_t max_len;           // upper bound on seq_lens[] (chooses the kernel):
   int32_t len_stated;        //   the caller's own (else the table's width)
+  int32_t spread;            // the order of the workgroups (set by the launcher)
   float scale_log2;
 };
 

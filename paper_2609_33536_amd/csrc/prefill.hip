@@ -459,7 +459,7 @@ struct Extent {
 };
 
 __device__ __forceinline__ PrefillPlace place(const PrefillArgs& a, int tiles) {
-  return place_workgroup(blockIdx.x, blockIdx.y, gridDim.x, gridDim.y, tiles, a.num_kv_heads, a.batch);
+  return place_workgroup(blockIdx.x, blockIdx.y, gridDim.x, gridDim.y, tiles, a.num_kv_heads, a.batch, a.spread != 0);
 }
 
 // ---- 4 waves x 32 columns over shared units --------------------------------
@@ -692,7 +692,8 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(1
 }
 
 template <typename T, int G, bool F8>
-hipError_t launch_typed(const PrefillArgs& a, bool elastic, hipStream_t st) {
+hipError_t launch_typed(PrefillArgs a, bool elastic, hipStream_t st) {
+  a.spread = spread_tiles((int64_t)a.batch * a.num_kv_heads, a.total_q, (int64_t)a.batch * a.max_q_len);
   constexpr int kSplitTok = kPfCols / G;
   const int64_t split = (int64_t)((a.max_q_len + kSplitTok - 1) / kSplitTok) * a.num_kv_heads * a.batch;
   // (EKV_PREFILL_SPLIT = 0 or 1 overrides, for tests and measurements)

@@ -34,6 +34,21 @@ inline bool divide_units(int64_t workgroups, int64_t columns, int max_len, bool 
          (workgroups <= 8 * kCus && columns <= 32 && stated && max_len >= 1024);
 }
 
+// Whether the tiles of a (sequence, KV head) are spread over the XCDs where the
+// number of KV heads is not a multiple of 8 (groups: batch * num_kv_heads; rows:
+// of all chunks; most_rows: if every chunk were as long as the longest).  Ids go
+// round robin over the 8 XCDs, so with groups a multiple of 8 every tile of a
+// (sequence, KV head) lands on one XCD: its K and V stay in one L2, but sequences
+// of unlike lengths load the XCDs unevenly.  So they are spread if the chunks
+// are ragged, or if an XCD would have fewer than 4 of them (an odd number of
+// groups spreads by itself).  Measured (us, one XCD / spread): 16 x (2048 + 512)
+// ragged, 16 / 1 heads 181 / 122, 32 / 4 heads 258 / 211; 16 x 0-1024, 16 / 2 heads 111
+// / 63; 64 chunks of up to 300 rows, 16 / 1 heads 73 / 52; alike, 16 x (2048 + 512),
+// 32 / 4 heads 460 / 489, 16 / 1 heads 231 / 238.
+inline bool spread_tiles(int64_t groups, int64_t rows, int64_t most_rows) {
+  return groups % 2 == 0 && (groups < 32 || 8 * rows < 7 * most_rows);
+}
+
 struct PrefillPlace {
   int seq, kv_head, tile;
 };
@@ -42,14 +57,13 @@ struct PrefillPlace {
 // (sequence, KV head), query tile; the last tiles (most keys) first.  Ids go
 // round robin over the 8 XCDs: with a multiple of 8 KV heads all tiles of one
 // (sequence, KV head) go to one XCD and share its L2, and every XCD gets a KV
-// head of every sequence; otherwise whole (sequence, KV head)s would load the
-// XCDs unevenly (12 of them: 1.4x the time), and the tiles are spread instead.
+// head of every sequence; otherwise see spread_tiles.
 // (Two grid dimensions only for the launch's size limits.  A grid of 2^31
 // workgroups or more has no 32-bit id and takes the dimensions as they are: a
 // batch of tens of thousands of sequences with one very long chunk, nearly all
 // of whose workgroups have nothing to do.)
 __host__ __device__ inline PrefillPlace place_workgroup(uint32_t bx, uint32_t by, uint32_t gx, uint32_t gy, int tiles,
-                                                        int num_kv_heads, int batch) {
+                                                        int num_kv_heads, int batch, bool spread) {
   if ((uint64_t)gx * gy >> 31)
     return {(int)by, (int)(bx % (uint32_t)num_kv_heads), tiles - 1 - (int)(bx / (uint32_t)num_kv_heads)};
   const int id = (int)(by * gx + bx);
@@ -60,8 +74,8 @@ __host__ __device__ inline PrefillPlace place_workgroup(uint32_t bx, uint32_t by
     tile = i % tiles;
   } else {
     const int groups = batch * num_kv_heads;
-    group = id % groups;
     tile = id / groups;
+    group = (id % groups + (spread ? tile : 0)) % groups;
   }
   return {group / num_kv_heads, group % num_kv_heads, tiles - 1 - tile};
 }

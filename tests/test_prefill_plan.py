@@ -14,9 +14,13 @@ from paper_2609_33536_amd import build
 
 SOURCE = """
 #include "prefill_plan.h"
-extern "C" void place(uint32_t bx, uint32_t by, uint32_t gx, uint32_t gy, int tiles, int hkv, int batch, int* out) {
-  const ekv::PrefillPlace p = ekv::place_workgroup(bx, by, gx, gy, tiles, hkv, batch);
+extern "C" void place(uint32_t bx, uint32_t by, uint32_t gx, uint32_t gy, int tiles, int hkv, int batch, int spread,
+                      int* out) {
+  const ekv::PrefillPlace p = ekv::place_workgroup(bx, by, gx, gy, tiles, hkv, batch, spread != 0);
   out[0] = p.seq, out[1] = p.kv_head, out[2] = p.tile;
+}
+extern "C" int spreads(int64_t groups, int64_t rows, int64_t most_rows) {
+  return ekv::spread_tiles(groups, rows, most_rows);
 }
 extern "C" int divides(int64_t workgroups, int64_t columns, int max_len, int stated) {
   return ekv::divide_units(workgroups, columns, max_len, stated != 0);
@@ -38,17 +42,38 @@ def plan(tmp_path_factory):
     return ctypes.CDLL(str(d / "plan.so"))
 
 
-def _place(plan, bx, by, gx, gy, tiles, hkv, batch):
+def _place(plan, bx, by, gx, gy, tiles, hkv, batch, spread=False):
     out = (ctypes.c_int * 3)()
-    plan.place(bx, by, gx, gy, tiles, hkv, batch, out)
+    plan.place(bx, by, gx, gy, tiles, hkv, batch, int(spread), out)
     return tuple(out)
 
 
 @pytest.mark.parametrize("tiles,hkv,batch", itertools.product([1, 2, 7], [1, 2, 3, 8, 16], [1, 3, 16]))
 def test_every_tile_once(plan, tiles, hkv, batch):
     gx, gy = tiles * hkv, batch
-    got = {_place(plan, bx, by, gx, gy, tiles, hkv, batch) for by in range(gy) for bx in range(gx)}
-    assert got == set(itertools.product(range(batch), range(hkv), range(tiles)))
+    for spread in (False, True):
+        got = {_place(plan, bx, by, gx, gy, tiles, hkv, batch, spread) for by in range(gy) for bx in range(gx)}
+        assert got == set(itertools.product(range(batch), range(hkv), range(tiles)))
+
+
+@pytest.mark.parametrize("hkv,batch", [(1, 16), (1, 64), (2, 8), (4, 16), (3, 16), (1, 18), (2, 3), (6, 2)])
+def test_spread_tiles_lie_on_all_xcds(plan, hkv, batch):
+    """16 tiles of every (sequence, KV head) on the 8 XCDs (workgroup ids go round robin): two on each where the
+    number of groups is a multiple of 8 (unspread: all 16 on one), else at most twice that on any."""
+    tiles, groups = 16, hkv * batch
+    assert plan.spreads(ctypes.c_int64(groups), ctypes.c_int64(1), ctypes.c_int64(2))
+    xcds = {}
+    for i in range(tiles * groups):
+        s, h, t = _place(plan, i % (tiles * hkv), i // (tiles * hkv), tiles * hkv, batch, tiles, hkv, batch, True)
+        xcds.setdefault((s, h), []).append(i % 8)
+    most = 2 if groups % 8 == 0 else 4
+    assert all(max(x.count(i) for i in range(8)) <= most for x in xcds.values())
+
+
+@pytest.mark.parametrize("groups,rows,most,spread", [(64, 7, 8, False), (64, 6999, 8000, True), (32, 7, 8, False),
+                                                     (30, 8, 8, True), (31, 1, 8, False), (65, 1, 8, False)])
+def test_choice_of_the_order(plan, groups, rows, most, spread):
+    assert bool(plan.spreads(ctypes.c_int64(groups), ctypes.c_int64(rows), ctypes.c_int64(most))) == spread
 
 
 @pytest.mark.parametrize("tiles,hkv,batch", [(16384, 8, 16384), (1 << 18, 8, 65535), (1 << 21, 3, 65535)])
