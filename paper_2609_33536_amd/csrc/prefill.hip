@@ -483,6 +483,14 @@ __device__ __forceinline__ PrefillPlace place(const PrefillArgs& a, int tiles) {
 // only every ~4.9 cycles: 4-6 % slower); the remainders p - head by
 // v_dot2_f32_bf16 (fewer instructions, but they occupy the matrix pipe: 5 % slower).
 constexpr int kPfRing = 4;
+// Contexts of at most kPfFew units skip the pipeline, whose fill and drain (the
+// loads past the last unit, a unit of products each before the first and after
+// the last) cost more there than it hides: the ring is filled with up to 4 units
+// at once, and a wave works through them without a barrier.  Measured (us, bf16,
+// pipeline / rounds): 64 prompts of up to 16 rows, 16 / 16 heads 12.9 / 10.4, of up
+// to 77 rows, 64 / 8 heads 47.8 / 44.7; 5-8 units, 16 x (200 + up to 77), 32 / 8
+// heads 20.0 / 18.2, 8-bit, 64 / 8 heads 26.4 / 24.8.
+constexpr int kPfFew = 8;
 
 template <typename T, int G, bool ELASTIC, bool F8>
 __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_kernel(PrefillArgs a) {
@@ -526,57 +534,86 @@ __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(2
     stager.widen(ring + slot_of(u), ELASTIC && ((modes >> (issued - 1 - u)) & 1u) != 0u, wave, 32 * u, valid, lane);
   };
 
-  u32x4 hi[2], lo[2], k[8], v[2][4];
+  if (units <= kPfFew) {
+#pragma unroll 1
+    for (int u0 = 0; u0 < units; u0 += kPfRing) {
+      const int u1 = min(units, u0 + kPfRing);
+      if (u0 > 0) barrier();   // every wave is done with the ring
+#pragma unroll 1
+      for (int u = u0; u < u1; ++u) issue();
+#pragma unroll 1
+      for (int u = u0; u < u1; ++u) stage(u, std::integral_constant<int, 0>{});
+      barrier();
+#pragma unroll 1
+      for (int u = u0; u < min(u1, own_units); ++u) {
+        u32x4 k[8], v[2][4], hi[2], lo[2];
+        read_k(k_at + slot_of(u), k);
+        read_v(v_at + slot_of(u), v);
+        f32x16 sc = col.scores(k);
+        const float c = col.mask(sc, 32 * u, h);
+        float shift;
+        if (col.advance(sc, c, &shift)) col.rescale(fast_exp2(shift));
+        col.l += col.probabilities(sc, c, col.m, hi, lo);
 #pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    hi[ks] = lo[ks] = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int t = 0; t < 4; ++t) v[ks][t] = u32x4{0u, 0u, 0u, 0u};
-  }
-  auto products = [&]() {   // O += V^T P^T of the unit whose P and V are in registers
+        for (int ks = 0; ks < 2; ++ks) {
+          col.accumulate(v[ks], hi[ks]);
+          col.accumulate(v[ks], lo[ks]);
+        }
+      }
+    }
+  } else {
+    u32x4 hi[2], lo[2], k[8], v[2][4];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      col.accumulate(v[ks], hi[ks]);
-      col.accumulate(v[ks], lo[ks]);
+      hi[ks] = lo[ks] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[ks][t] = u32x4{0u, 0u, 0u, 0u};
     }
-  };
-#pragma unroll 1
-  for (int u = 0; u < kPfRing - 1; ++u) issue();
-  stage(0, std::integral_constant<int, kPfRing - 2>{});
-  stage(1, std::integral_constant<int, kPfRing - 3>{});
-  barrier();
-  read_k(k_at, k);
-  f32x16 sc = col.scores(k);
-
-#pragma unroll 1
-  for (int i = 0; i < units; ++i) {
-    barrier();   // units i and i + 1 are whole; unit i - 1's slot is free
-    issue();
-    if (i < own_units) {
-      const float c = col.mask(sc, 32 * i, h);
-      float shift;
-      const bool moved = col.advance(sc, c, &shift);
-      read_k(k_at + slot_of(i + 1), k);
-      products();
-      read_v(v_at + slot_of(i), v);
-      const f32x16 next = col.scores(k);
-      u32x4 nhi[2], nlo[2];
-      float sum = col.probabilities(sc, c, col.m, nhi, nlo);
-      // (kept in this block, beside the products: not sunk below the rescale's branch)
-      asm volatile("" : "+v"(nhi[0]), "+v"(nhi[1]), "+v"(nlo[0]), "+v"(nlo[1]), "+v"(sum));
+    auto products = [&]() {   // O += V^T P^T of the unit whose P and V are in registers
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        hi[ks] = nhi[ks];
-        lo[ks] = nlo[ks];
+        col.accumulate(v[ks], hi[ks]);
+        col.accumulate(v[ks], lo[ks]);
       }
-      sc = next;
-      if (moved) col.rescale(fast_exp2(shift));   // (unit i - 1's products, under the old reference, are in)
-      col.l += sum;
+    };
+#pragma unroll 1
+    for (int u = 0; u < kPfRing - 1; ++u) issue();
+    stage(0, std::integral_constant<int, kPfRing - 2>{});
+    stage(1, std::integral_constant<int, kPfRing - 3>{});
+    barrier();
+    read_k(k_at, k);
+    f32x16 sc = col.scores(k);
+
+#pragma unroll 1
+    for (int i = 0; i < units; ++i) {
+      barrier();   // units i and i + 1 are whole; unit i - 1's slot is free
+      issue();
+      if (i < own_units) {
+        const float c = col.mask(sc, 32 * i, h);
+        float shift;
+        const bool moved = col.advance(sc, c, &shift);
+        read_k(k_at + slot_of(i + 1), k);
+        products();
+        read_v(v_at + slot_of(i), v);
+        const f32x16 next = col.scores(k);
+        u32x4 nhi[2], nlo[2];
+        float sum = col.probabilities(sc, c, col.m, nhi, nlo);
+        // (kept in this block, beside the products: not sunk below the rescale's branch)
+        asm volatile("" : "+v"(nhi[0]), "+v"(nhi[1]), "+v"(nlo[0]), "+v"(nlo[1]), "+v"(sum));
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          hi[ks] = nhi[ks];
+          lo[ks] = nlo[ks];
+        }
+        sc = next;
+        if (moved) col.rescale(fast_exp2(shift));   // (unit i - 1's products, under the old reference, are in)
+        col.l += sum;
+      }
+      stage(i + 2, std::integral_constant<int, kPfRing - 3>{});
     }
-    stage(i + 2, std::integral_constant<int, kPfRing - 3>{});
+    wait_loads<0>();   // no load may land after the workgroup has ended
+    products();
   }
-  wait_loads<0>();   // no load may land after the workgroup has ended
-  products();
 
   const float inv = 1.0f / col.total();
   if (col.ok) {

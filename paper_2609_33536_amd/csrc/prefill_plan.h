@@ -11,7 +11,10 @@ namespace ekv {
 // prefill_split_kernel (`columns`: the longest chunk's; max_len: the context
 // bound, stated by the caller or the table's width).  Measured (us, bf16, half
 // BASE, 128-column / split kernel):
-//  - up to 256 workgroups (one a CU): always.  128 workgroups of 8 rows over
+//  - contexts of one unit and at most 64 columns: never (three waves would have
+//    no unit).  4 prompts of up to 32 rows, 16 / 16 heads 6.0 / 6.7, 8-bit 6.1 / 7.0;
+//    12 of up to 16 rows, 32 / 8 heads 6.6 / 7.0 (but 32 rows 8.6 / 6.7 for one);
+//  - else up to 256 workgroups (one a CU): always.  128 workgroups of 8 rows over
 //    16-215 keys 12.9 / 10.1, over 4096 112 / 57;
 //  - up to 512 over contexts of at least 512 keys, where a quarter of the chain
 //    saves more than the second round's start and merge cost: 384 and 512
@@ -30,6 +33,7 @@ namespace ekv {
 //    33.9, 49 / 64).
 inline bool divide_units(int64_t workgroups, int64_t columns, int max_len, bool stated) {
   constexpr int64_t kCus = 256;
+  if (stated && max_len <= 32 && columns <= 64) return false;
   return workgroups <= kCus || (workgroups <= 2 * kCus && max_len >= 512) ||
          (workgroups <= 8 * kCus && columns <= 32 && stated && max_len >= 1024);
 }

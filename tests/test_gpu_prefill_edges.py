@@ -52,6 +52,22 @@ def test_prefill_tile_unit_and_ring_edges(group, hkv, dtype, fraction, split, mo
 
 
 @pytest.mark.parametrize("split", [True, False])
+@pytest.mark.parametrize("fraction", [0.0, 0.5])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16", "e5m2"])
+@pytest.mark.parametrize("group,hkv", [(4, 8), (16, 2), (1, 3)])
+def test_prefill_contexts_of_few_units(group, hkv, dtype, fraction, split, monkeypatch):
+    """Contexts around 4 and 8 units (128 and 256 keys): the 128-column kernel
+    takes up to 8 in rounds of 4 and pipelines longer ones; the tiles of one chunk
+    fall on both sides, and waves have no unit."""
+    monkeypatch.setenv("EKV_PREFILL_SPLIT", "1" if split else "0")
+    total = [96, 127, 128, 129, 160, 161, 255, 256, 257, 288, 289, 320]
+    chunk = [96, 1, 31, 129, 33, 2, 128 // group + 1, 256, 130, 32, 289, 64]
+    case = workloads.make_prefill_case([t - c for t, c in zip(total, chunk)], chunk, group * hkv, hkv, dtype=dtype,
+                                       seed=215, base_fraction=fraction, spare_blocks=2)
+    _run(case, group * hkv, hkv)
+
+
+@pytest.mark.parametrize("split", [True, False])
 @pytest.mark.parametrize("dtype", ["bf16", "e5m2"])
 @pytest.mark.parametrize("placement,fraction", [("random", 0.5), ("oldest", 0.5), ("random", 0.0)])
 def test_prefill_metadata_window_edges(placement, fraction, dtype, split, monkeypatch):

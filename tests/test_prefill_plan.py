@@ -90,6 +90,7 @@ def test_grids_beyond_31_bits(plan, tiles, hkv, batch):
 
 
 @pytest.mark.parametrize("workgroups,columns,max_len,stated,split", [
+    (1, 64, 32, True, False), (1, 65, 32, True, True), (1, 64, 33, True, True), (1, 64, 32, False, True),   # one unit
     (1, 4096, 16, False, True), (256, 4096, 16, False, True),                       # they fit the chip at once
     (257, 64, 511, True, False), (257, 64, 512, False, True), (512, 64, 512, True, True), (513, 64, 8192, True, False),
     (513, 32, 1024, True, True), (2048, 32, 8192, True, True), (2049, 32, 8192, True, False),
