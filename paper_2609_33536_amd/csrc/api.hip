@@ -87,12 +87,15 @@ int max_seq_blocks(const ekv_batch* b) {
 // sequence's pairs, at most 8.  A workgroup alone takes ~1.5 us a pair, so a
 // small batch is spread over the chip; but a merge reads 64 / G pieces per
 // memory round trip, so ranges far below 1 / 32 cost more in the merge than
-// they save in the stream.  Measured (bf16, 32 / 8 heads unless said; ranges of 1 / 2 /
-// this rule / 8 pairs, us): 4 sequences of 64-256 tokens, 8 / 2 heads 9.2 / 10.8 / 9.1 /
-// 19.3; 1 x 4096 17.6 / 12.4 / 11.5 (4 pairs) / 14.8; 8 x 512-2048 15.6 / 15.6 /
-// 15.6 / 19.5; 8-bit pool 4 x 1000-4000 21.8 / 19.0 / 16.9 / 19.1; from ~8192 tokens on the
-// rule gives 8, and from ~1024 ranges of 8 pairs in the batch on every launch
-// fills the chip and the rule has no effect.
+// they save in the stream.  Measured (us, bf16, half BASE; ranges of 1 / 2 / this
+// rule's / 8 pairs, at G = 1, 4, 8 and 16):
+//   1 x 1024  (1)  7.1 / 8.5 / 7.2 / 16   8.8 / 8.8 / 8.7 / 16   11 / 11 / 11 / 20   16 / 14 / 16 / 22
+//   1 x 4096  (4)  11 / 9.3 / 11 / 16     19 / 13 / 13 / 17      30 / 19 / 18 / 22   47 / 29 / 22 / 26
+//   8 x 512-2048 (2) 14 / 14 / 14 / 19    16 / 16 / 16 / 20      20 / 20 / 20 / 26   25 / 26 / 26 / 30
+// and 4 sequences of 64-256 tokens 7-9 with 1, 21-26 with 8.  (Pieces to fit 64 / G
+// would do better at the ends: G = 1, 1 x 8192 16 -> 12 with 2; G = 16, 1 x 1024 with 2.)
+// From ~8192 tokens on the rule gives 8, and from ~1024 ranges of 8 pairs in the
+// batch on every launch fills the chip and the rule has no effect.
 // EKV_MIN_CHUNK (forced, 0: unset) overrides.
 constexpr int kMostPairs = 8, kPieces = 32;
 int forced_min_chunk() {
@@ -333,7 +336,8 @@ ekv_status decode_call(const ekv_pool* pool, const ekv_batch* batch, const void*
       return fail(EKV_ERR_INVALID, "%s: ws must be 16-byte aligned", who);
   }
   int grids[2] = {0, 0};
-  if ((st = device_grids(pool, group, plan, grids)) != EKV_OK)   // (without a device's grid only the reported size is known to do)
+  // (without a device's grid only the reported size is known to do)
+  if ((st = device_grids(pool, group, plan, grids)) != EKV_OK)
     return !clear_counters && ws_bytes < reported ? too_small() : st;
   const size_t least = decode_layout(std::min<long long>(std::max(grids[0], grids[1]), plan.coarsest), group).total;
   if (least > ws_bytes)   // (the static scratch: sized by the device's own grid)

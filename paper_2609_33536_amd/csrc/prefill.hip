@@ -27,10 +27,11 @@
 // BASE) are loaded raw and widened in place, once per workgroup (a wave widens
 // the quarter that it loaded).  When every wave fetched and widened the BASE
 // operands for itself, a unit cost a wave 182 vector, 110 scalar and 21 branch
-// instructions; now ~140, ~55 and ~8.
+// instructions (its 24 products aside); now 147, 59 and 9.
 //
 // Two kernels:
-//   prefill_kernel        4 waves x 32 columns share every unit;
+//   prefill_kernel        4 waves x 32 columns share every unit (pipelined, or
+//                         in rounds of 4 units over contexts of at most 8);
 //   prefill_split_kernel  4 waves share 32 columns and take every fourth unit
 //                         each: small launches, which leave most CUs idle.
 #include <cstdlib>
@@ -468,7 +469,7 @@ __device__ __forceinline__ PrefillPlace place(const PrefillArgs& a, int tiles) {
 // scores of unit i + 1 (both in the same basic block, so the compiler
 // interleaves them), reads K of unit i + 1 and V of unit i, widens unit i + 2
 // and issues the loads of unit i + 3.  4 slots, 66,560 B of LDS: two
-// workgroups, two waves per SIMD (232 registers).
+// workgroups, two waves per SIMD (228-236 registers).
 // Measured in one run against the kernel before (32-key units fetched and
 // widened per wave, no pipeline), append of the chunk included: 8B chunked
 // prefill (16 x (2048 prefix, half BASE, + 512), 32 / 8 heads, bf16) 537 ->
