@@ -148,7 +148,9 @@ __device__ __forceinline__ int piece_slot(int w_first, int first_odd, int k) {
 // writes, and ~5 % of an f = 1 launch's time).  The workspace is 16-byte
 // aligned (checked at the entry point).
 __device__ __forceinline__ void store_agent_f4(float* p, f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+  // (a vector instruction may overwrite a wide store's data 2 wait states after it; the compiler keeps that
+  // distance for its own stores only)
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 // 16-byte loads with the same policy, through a buffer descriptor of the
 // partial rows (the compiler tracks them; its bound is the launch's slots).
